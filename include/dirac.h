@@ -167,8 +167,8 @@ int dirac_force(dirac_op op, const void* U, const void* psi, const void* chi, vo
  * dirac_brillouin_links_backward: gV += dL/dV for L(W(V)) given gW = dL/dW on the 40 stored directions of
  *   dirac_brillouin_links (Tab. off-axis: path averages of V).
  * FP64 only: U, V, gU, gV complex128 [s][4][nc][nc]; gW complex128 [s][40][nc][nc].  Outputs must not overlap
- * the inputs.  The backward calls add with atomics: the summation order, and so the last bits, can vary
- * from run to run.  Errors: EINVAL, EUNSUPPORTED (nc), EHIP.
+ * the inputs.  The backward calls add to their outputs with atomics; in dirac_stout_backward many adds meet in one
+ * element, so its summation order, and so the last bits, can vary from run to run.  Errors: EINVAL, EUNSUPPORTED (nc), EHIP.
  */
 int dirac_stout_smear(const void* U, void* V, double rho, int nc, const dirac_dims* dims, void* stream);
 int dirac_stout_backward(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,

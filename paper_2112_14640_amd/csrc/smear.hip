@@ -8,8 +8,10 @@
 // dL = Re Tr(G^+ dM).  For a product the gradient of a factor is (left part)^+ G (right part)^+; for
 // E = exp(X) it is L(X^+, G_E), the Frechet derivative of exp at X^+ in the direction G_E (the adjoint
 // of L(X, .) for this inner product), read off the upper right block of exp([[X^+, G_E], [0, X^+]]).
-// All arithmetic FP64 (complex128 links and gradients).  Gradients are accumulated with atomic adds, so
-// the order of the additions (and the last bits of the result) can differ from run to run.
+// All arithmetic FP64 (complex128 links and gradients).  The stout gradients are accumulated with atomic adds,
+// so the order of the additions (and the last bits of the result) can differ from run to run.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -290,85 +292,237 @@ __global__ __launch_bounds__(64) void stout_backward_kernel(const double2* __res
     }
 }
 
-// gV += the gradient with respect to V of L(W(V)) given gW = dL/dW for the 40 stored directions:
-// W_d(n) = (1/|d|!) sum over the orderings of the unit steps of the path products, a step -mu from x
-// contributing V_mu(x-mu)^+.  One thread per (stored direction, site).
-__device__ __forceinline__ bool next_perm(int* a, int k) {
-    int i = k - 2;
-    while (i >= 0 && a[i] >= a[i + 1]) --i;
-    if (i < 0) return false;
-    int j = k - 1;
-    while (a[j] <= a[i]) --j;
-    int t = a[i];
-    a[i] = a[j];
-    a[j] = t;
-    for (int l = i + 1, r = k - 1; l < r; ++l, --r) {
-        t = a[l];
-        a[l] = a[r];
-        a[r] = t;
+// ---------------------------------------------------------------------------
+// gV += the gradient with respect to V of L(W(V)) given gW = dL/dW for the 40 stored directions.
+//
+// A path of W_d that uses V_mu(m) forwards splits there into a prefix of displacement a (from n = m - a to m) and a
+// suffix of displacement b (from m + mu), d = a + e_mu + b, with a and b in the three other axes and of disjoint
+// support.  The paths with the same split are the products W_a(n) V_mu(m) W_b(m + mu), with weight
+// |a|! |b|! / |d|!, and W_a(n)^+ = W_{-a}(m), so
+//   gV_mu(m) = sum_{a, b} |a|! |b|! / |d|! W_{-a}(m) G_d(m - a) W_b(m + mu)^+
+// over the 125 pairs (a, b), where G_d is gW for a stored d and, since W_d(n) = W_{-d}(n + d)^+, the adjoint of
+// gW_{-d}(n + d) otherwise (a path that uses V_mu(m) backwards is the reverse of one counted here).  Every output
+// is a gather with a fixed order of summation and is added to gV once.
+//
+// A work-group takes kSplitSites consecutive sites and one mu (blocks of the four mu of a tile are neighbours and
+// share the gW lines in L2).  It builds the 26 path averages in the three other axes at m and at m + mu in LDS, level
+// by level, one row of a matrix per thread; then a thread owns one column of the output and one of 16 groups of
+// pairs, so a product with a pair is a matrix-vector product, and the groups are added across 16 lanes.  The groups
+// hold at most 9 pairs each (a = 0 in three groups, |a| = 1 one group each, the rest in seven), which balances them
+// to within a tenth.  Bound by the address rate of the gW and V loads (16 bytes a lane, a matrix a few lanes).
+// Separate walks along all 1108 paths of a site, with an atomic add per factor, took 7.44 ms at 8^3 x 16 (N_c = 3);
+// this takes 0.23 ms.
+// ---------------------------------------------------------------------------
+constexpr int kSplitSites = 4;
+constexpr int kSplitGroups = 16;
+constexpr int kSplitPairs = 9;  // the largest group
+
+// Displacements in the three other axes are numbered c = 9 (c_2 + 1) + 3 (c_1 + 1) + c_0 + 1 (13: none; -c: 26 - c).
+constexpr int trans_digit(int c, int q) { return (q == 0 ? c : (q == 1 ? c / 3 : c / 9)) % 3 - 1; }
+constexpr int trans_order(int c) { return (trans_digit(c, 0) != 0) + (trans_digit(c, 1) != 0) + (trans_digit(c, 2) != 0); }
+constexpr int trans_axis(int mu, int q) { return q + (q >= mu); }
+
+// The pairs of one mu, packed, since decoding them with divisions cost more than the products (277 us at 8^3 x 16):
+// bits 0-4 26 - a, 5-9 b, 10-15 the stored direction, 16 whether its adjoint is G_d, 17 last pair of this a, 18-21
+// 4 |a| + |b|, 22-26 the displacement of the site that holds it (from m, or from m + mu for an adjoint).
+struct SplitTable {
+    uint32_t pair[4][kSplitGroups][kSplitPairs];
+    int count[kSplitGroups];
+};
+constexpr SplitTable make_split_table() {
+    SplitTable t{};
+    for (int mu = 0; mu < 4; ++mu) {
+        int n0 = 0, n1 = 0, n2 = 0, n3 = 0;
+        int cnt[kSplitGroups] = {};
+        for (int order = 0; order < 4; ++order)
+            for (int a = 0; a < 27; ++a) {
+                if (trans_order(a) != order) continue;
+                // |a| = 2 (3 pairs each): two to each of groups 9..14; |a| = 3 (1 pair): five to group 15, three more
+                const int ga = order == 1 ? 3 + n1 : (order == 2 ? 9 + n2 / 2 : (n3 < 5 ? 15 : 4 + n3));
+                int grp = ga;
+                for (int b = 0; b < 27; ++b) {
+                    int num = 40, stride[4] = {1, 3, 9, 27};
+                    bool disjoint = true;
+                    num += stride[mu];
+                    for (int q = 0; q < 3; ++q) {
+                        const int da = trans_digit(a, q), db = trans_digit(b, q);
+                        if (da != 0 && db != 0) disjoint = false;
+                        num += (da + db) * stride[trans_axis(mu, q)];
+                    }
+                    if (!disjoint) continue;
+                    if (order == 0) grp = n0++ / 9;
+                    const bool adj = num > 40;  // -d is stored, at n + d = m + mu + b; else d, at n = m - a
+                    t.pair[mu][grp][cnt[grp]++] =
+                        static_cast<uint32_t>((26 - a) | b << 5 | (adj ? 80 - num : num) << 10 | (adj ? 1 : 0) << 16 |
+                                              (order * 4 + trans_order(b)) << 18 | (adj ? b : 26 - a) << 22);
+                }
+                n1 += order == 1;
+                n2 += order == 2;
+                n3 += order == 3;
+            }
+        for (int grp = 0; grp < kSplitGroups; ++grp) {
+            t.count[grp] = cnt[grp];
+            for (int e = 0; e < cnt[grp]; ++e)
+                if (e + 1 == cnt[grp] || (t.pair[mu][grp][e] & 31u) != (t.pair[mu][grp][e + 1] & 31u))
+                    t.pair[mu][grp][e] |= 1u << 17;
+        }
     }
-    return true;
+    return t;
 }
+__constant__ SplitTable c_split = make_split_table();
+struct TransDirs {
+    unsigned char dir[26];  // 6 of order 1, 12 of order 2, 8 of order 3
+};
+constexpr TransDirs make_trans_dirs() {
+    TransDirs t{};
+    int n = 0;
+    for (int order = 1; order < 4; ++order)
+        for (int a = 0; a < 27; ++a)
+            if (trans_order(a) == order) t.dir[n++] = static_cast<unsigned char>(a);
+    return t;
+}
+__constant__ TransDirs c_trans = make_trans_dirs();
 
 template <int NC>
-__global__ __launch_bounds__(64) void links_backward_kernel(const double2* __restrict__ V, const double2* __restrict__ GW,
-                                                            double2* __restrict__ GV, Geom g) {
-    const int64_t gid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (gid >= 40 * g.vol) return;
-    const int dir = static_cast<int>(gid / g.vol);
-    const int64_t site = gid - static_cast<int64_t>(dir) * g.vol;
-    const int d[4] = {dir % 3 - 1, (dir / 3) % 3 - 1, (dir / 9) % 3 - 1, dir / 27 - 1};
-    int smu[4], ssg[4], k = 0;
-    for (int mu = 0; mu < 4; ++mu)
-        if (d[mu] != 0) {
-            smu[k] = mu;
-            ssg[k] = d[mu];
-            ++k;
-        }
-    const Coord c0 = site_coord(site, g);
-    const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
-    CM<NC> G;
-    {
-        const double2* p = GW + (site * 40 + dir) * NC * NC;
-        for (int a = 0; a < NC; ++a)
-            for (int b = 0; b < NC; ++b) G.e[a][b] = {p[a * NC + b].x, p[a * NC + b].y};
-    }
-    double fact = 1.0;
-    for (int j = 2; j <= k; ++j) fact *= j;
-    G = scaled(G, cx<double>{1.0 / fact, 0.0});
-    int perm[4] = {0, 1, 2, 3};
-    do {
-        // the links of this path and the sites/directions of the V they come from
-        CM<NC> L[4];
-        int64_t lsite[4];
-        int lmu[4];
-        bool ladj[4];
+__global__ __launch_bounds__(kSplitSites * kSplitGroups * NC) void links_backward_kernel(
+    const double2* __restrict__ V, const double2* __restrict__ GW, double2* __restrict__ GV, Geom g) {
+    constexpr int S = kSplitSites, L = NC * NC, T = S * kSplitGroups * NC;
+    __shared__ cx<double> w[S][2][27][L];  // path averages in the three other axes at m and m + mu (13: identity)
+    __shared__ int disp[S][2][27];         // their sites' offsets from m (32 bits: V < 2^31)
+    __shared__ uint32_t pairs[kSplitGroups * kSplitPairs];
+    const int64_t block = logical_block();
+    const int mu = static_cast<int>(block & 3);
+    const int64_t site0 = (block >> 2) * S;
+    if (site0 >= g.vol) return;
+    const int ns = static_cast<int>(g.vol - site0 < S ? g.vol - site0 : S);
+    const int tid = threadIdx.x;
+    const int ax[3] = {trans_axis(mu, 0), trans_axis(mu, 1), trans_axis(mu, 2)};
+    for (int u = tid; u < kSplitGroups * kSplitPairs; u += T) pairs[u] = c_split.pair[mu][0][u];
+    for (int u = tid; u < S * 54; u += T) {
+        const int s = u / 54, pc = u % 54, c = pc % 27;
+        const Coord c0 = site_coord(site0 + (s < ns ? s : 0), g);
         int x[4] = {c0.x, c0.y, c0.z, c0.t};
-        for (int j = 0; j < k; ++j) {
-            const int mu = smu[perm[j]];
-            if (ssg[perm[j]] > 0) {
-                lsite[j] = site_index(x[0], x[1], x[2], x[3], g);
-                ladj[j] = false;
-                x[mu] = wrap(x[mu] + 1, ext[mu]);
-            } else {
-                x[mu] = wrap(x[mu] - 1, ext[mu]);
-                lsite[j] = site_index(x[0], x[1], x[2], x[3], g);
-                ladj[j] = true;
+        const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
+#pragma unroll
+        for (int nu = 0; nu < 4; ++nu) {
+            int v = nu == mu ? pc / 27 : 0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                if (ax[q] == nu) v = trans_digit(c, q);
+            x[nu] = wrap(x[nu] + v, ext[nu]);
+        }
+        disp[s][pc / 27][c] =
+            static_cast<int>(site_index(x[0], x[1], x[2], x[3], g) - site0);
+    }
+    for (int u = tid; u < S * 2 * L; u += T) {
+        const int e = u % L;
+        w[u / (2 * L)][(u / L) & 1][13][e] = {e % (NC + 1) == 0 ? 1.0 : 0.0, 0.0};
+    }
+    __syncthreads();
+
+    auto level = [&](auto order_c) __attribute__((always_inline)) {
+        constexpr int ORDER = decltype(order_c)::value;
+        constexpr int FIRST = ORDER == 1 ? 0 : (ORDER == 2 ? 6 : 18), CNT = ORDER == 1 ? 6 : (ORDER == 2 ? 12 : 8);
+        for (int u = tid; u < ns * 2 * CNT * NC; u += T) {
+            const int i = u % NC, q = u / NC;
+            const int dir = c_trans.dir[FIRST + q % CNT];
+            const int p = (q / CNT) & 1, s = q / (2 * CNT);
+            const double2* lp[ORDER];
+            int prev[ORDER];
+            bool fwd[ORDER];
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int step = trans_digit(dir, k);
+                const int pv = dir - step * (k == 0 ? 1 : (k == 1 ? 3 : 9));  // one step shorter
+                // the last step's link: V_nu(n + d - e_nu) forwards, V_nu(n + d)^+ backwards
+                const double2* l = V + ((site0 + disp[s][p][step > 0 ? pv : dir]) * 4 + ax[k]) * L;
+#pragma unroll
+                for (int o = 0; o < ORDER; ++o)
+                    if (step != 0 && n == o) {
+                        lp[o] = l;
+                        prev[o] = pv;
+                        fwd[o] = step > 0;
+                    }
+                n += step != 0;
             }
-            lmu[j] = mu;
-            const CM<NC> v = load_link<NC>(V, lsite[j], mu);
-            L[j] = ladj[j] ? adj(v) : v;
+            cx<double> row[NC];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) row[j] = {0.0, 0.0};
+#pragma unroll
+            for (int o = 0; o < ORDER; ++o) {
+                const cx<double>* pr = &w[s][p][prev[o]][i * NC];
+#pragma unroll
+                for (int e = 0; e < NC; ++e)
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) {
+                        const double2 v = lp[o][fwd[o] ? e * NC + j : j * NC + e];
+                        cfma(row[j], pr[e], cx<double>{v.x, fwd[o] ? v.y : -v.y});
+                    }
+            }
+#pragma unroll
+            for (int j = 0; j < NC; ++j) w[s][p][dir][i * NC + j] = cscale(1.0 / ORDER, row[j]);
         }
-        // gradient of factor j: (L_0 .. L_{j-1})^+ G (L_{j+1} .. L_{k-1})^+
-        CM<NC> pre = ident<NC>();
-        for (int j = 0; j < k; ++j) {
-            CM<NC> suf = ident<NC>();
-            for (int l = j + 1; l < k; ++l) suf = mul(suf, L[l]);
-            const CM<NC> gl = mul(mul(adj(pre), G), adj(suf));
-            atomic_add_link<NC>(GV, lsite[j], lmu[j], ladj[j] ? adj(gl) : gl);
-            pre = mul(pre, L[j]);
+        __syncthreads();
+    };
+    level(std::integral_constant<int, 1>{});
+    level(std::integral_constant<int, 2>{});
+    level(std::integral_constant<int, 3>{});
+
+    const int grp = tid % kSplitGroups;
+    const int j = (tid / kSplitGroups) % NC;
+    const int s = tid / (kSplitGroups * NC);
+    if (s >= ns) return;
+    cx<double> col[NC], in[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) col[i] = in[i] = {0.0, 0.0};
+    const int cnt = c_split.count[grp];
+    for (int e = 0; e < cnt; ++e) {
+        const uint32_t pk = pairs[grp * kSplitPairs + e];
+        const int kab = (pk >> 18) & 15, ka = kab >> 2, kb = kab & 3;
+        const bool adj = (pk >> 16) & 1;
+        const double fa = ka == 3 ? 6.0 : (ka == 2 ? 2.0 : 1.0), fb = kb == 3 ? 6.0 : (kb == 2 ? 2.0 : 1.0);
+        const double wt = fa * fb * (ka + kb == 3 ? 1.0 / 24.0 : (ka + kb == 2 ? 1.0 / 6.0 : (ka + kb == 1 ? 0.5 : 1.0)));
+        const double2* gp = GW + ((site0 + disp[s][adj ? 1 : 0][pk >> 22]) * 40 + ((pk >> 10) & 63)) * L;
+        const cx<double>* wb = &w[s][1][(pk >> 5) & 31][j * NC];  // column j of W_b(m + mu)^+: row j conjugated
+        const int si = adj ? 1 : NC, sk = adj ? NC : 1;
+        const double sg = adj ? -1.0 : 1.0;
+        double2 z[L];
+#pragma unroll
+        for (int i = 0; i < NC; ++i)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) z[i * NC + k] = gp[i * si + k * sk];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const cx<double> v{wt * wb[k].re, -wt * wb[k].im};
+#pragma unroll
+            for (int i = 0; i < NC; ++i) cfma(in[i], cx<double>{z[i * NC + k].x, sg * z[i * NC + k].y}, v);
         }
-    } while (next_perm(perm, k));
+        if ((pk >> 17) & 1) {  // the last pair of this a: apply W_{-a}(m)
+            const cx<double>* wa = w[s][0][pk & 31];
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+                for (int k = 0; k < NC; ++k) cfma(col[i], wa[i * NC + k], in[k]);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) in[i] = {0.0, 0.0};
+        }
+    }
+#pragma unroll
+    for (int h = 1; h < kSplitGroups; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            col[i].re += __shfl_xor(col[i].re, h, kSplitGroups);
+            col[i].im += __shfl_xor(col[i].im, h, kSplitGroups);
+        }
+    if (grp == 0) {
+        double* o = reinterpret_cast<double*>(GV + ((site0 + s) * 4 + mu) * L + j);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {  // one add per element; atomic, so calls on two streams may share gV
+            atomicAdd(o + 2 * i * NC, col[i].re);
+            atomicAdd(o + 2 * i * NC + 1, col[i].im);
+        }
+    }
 }
 
 template <int NC>
@@ -385,9 +539,9 @@ int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out,
         hipLaunchKernelGGL((stout_backward_kernel<NC>), dim3(static_cast<unsigned>((4 * g.vol + block - 1) / block)),
                            dim3(block), 0, st, A, B, O, rho, g);
     } else {
-        const int block = 64;
-        hipLaunchKernelGGL((links_backward_kernel<NC>), dim3(static_cast<unsigned>((40 * g.vol + block - 1) / block)),
-                           dim3(block), 0, st, A, B, O, g);
+        const int64_t blocks = (g.vol + kSplitSites - 1) / kSplitSites * 4;
+        hipLaunchKernelGGL((links_backward_kernel<NC>), dim3(static_cast<unsigned>(grid_blocks_x8(blocks, 1))),
+                           dim3(kSplitSites * kSplitGroups * NC), 0, st, A, B, O, g);
     }
     return DIRAC_OK;
 }

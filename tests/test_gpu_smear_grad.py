@@ -73,6 +73,24 @@ def test_links_backward_against_differences(nc):
         assert abs(_rdot(gV, E) - want) < 1e-7 * max(1.0, abs(want)), (k, _rdot(gV, E), want)
 
 
+@pytest.mark.parametrize("nc,dims", [(1, (3, 2, 5, 3)), (2, (3, 3, 3, 5)), (3, (5, 3, 3, 3)), (4, (2, 3, 2, 3)),
+                                     (3, (2, 2, 2, 2))])
+def test_links_backward_ragged_tiles(nc, dims):
+    """Every colour count, volumes that leave the last tile of sites partly empty, wrapping extents of 2, and an
+    output that is added to; the tolerance is that of the central difference (truncation eps^2, cancellation
+    1e-16 |L| / eps)."""
+    rng = np.random.default_rng(660 + nc)
+    V = si.gauge_field(rng, dims, nc, "haar")
+    R = _cg(rng, dims[::-1] + (40, nc, nc))
+    base = _cg(rng, V.shape)
+    gV = host(dirac.brillouin_links_backward(to_dev(V), to_dev(R), out=to_dev(base))) - base
+    E = _cg(rng, V.shape)
+    want = _fd(lambda v: float(np.sum(np.conj(R) * brillouin_links(v)).real), V, E)
+    assert abs(_rdot(gV, E) - want) < 1e-7 * max(1.0, abs(want))
+    again = host(dirac.brillouin_links_backward(to_dev(V), to_dev(R), out=to_dev(base))) - base
+    assert np.array_equal(gV, again)
+
+
 @pytest.mark.parametrize("apbc", [True, False])
 def test_brillouin_force_against_differences(apbc):
     """g = d Re(psi^+ D_B(W) chi)/dW: L is linear in W, so the central difference is exact."""
