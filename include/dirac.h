@@ -173,6 +173,11 @@ int dirac_force(dirac_op op, const void* U, const void* psi, const void* chi, vo
 int dirac_stout_smear(const void* U, void* V, double rho, int nc, const dirac_dims* dims, void* stream);
 int dirac_stout_backward(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,
                          void* stream);
+/* dirac_stout_backward with a device workspace of ws_bytes >= two link fields (8 nc^2 complex128 per site), which must
+ * not overlap the arguments: the same gradient, gathered in a fixed order instead of added with atomics (faster, and
+ * bitwise reproducible into a gU of zeros).  Errors: also EINVAL (workspace NULL, misaligned or overlapping), EWORKSPACE. */
+int dirac_stout_backward_ws(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,
+                            void* workspace, size_t ws_bytes, void* stream);
 int dirac_brillouin_links_backward(const void* V, const void* gW, void* gV, int nc, const dirac_dims* dims,
                                    void* stream);
 

@@ -66,6 +66,7 @@ SIGNATURES = {
     "dirac_project_su": (_i, [_vp, _vp, _vp, _i, _i64, _vp]),
     "dirac_stout_smear": (_i, [_vp, _vp, _d, _i, _dims, _vp]),
     "dirac_stout_backward": (_i, [_vp, _vp, _vp, _d, _i, _dims, _vp]),
+    "dirac_stout_backward_ws": (_i, [_vp, _vp, _vp, _d, _i, _dims, _vp, _sz, _vp]),
     "dirac_brillouin_links_backward": (_i, [_vp, _vp, _vp, _i, _dims, _vp]),
     "dirac_blas_workspace_bytes": (_sz, [_i]),
     "dirac_norm2": (_i, [_i, _vp, _i64, _i, _vp, _vp, _sz, _vp]),

@@ -284,18 +284,35 @@ int dirac_stout_smear(const void* U, void* V, double rho, int nc, const dirac_di
     return DIRAC_OK;
 }
 
-int dirac_stout_backward(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,
-                         void* stream) {
+static int stout_backward(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,
+                          bool with_ws, void* ws, size_t ws_bytes, void* stream) {
     Geom g;
     int rc = link_call(U, true, gV, gU, nc, dims, g);
     if (rc) return rc;
     if (!std::isfinite(rho)) return fail(DIRAC_EINVAL, "rho is not finite");
     const size_t b = gauge_bytes(DIRAC_WILSON, DIRAC_FP64, nc, g);
     if (overlap(U, b, gU, b) || overlap(gV, b, gU, b)) return fail(DIRAC_EINVAL, "gU overlaps U or gV");
-    rc = launch_stout_backward(nc, g, U, gV, gU, rho, as_stream(stream));
+    if (with_ws) {
+        if (!ws) return fail(DIRAC_EINVAL, "NULL workspace");
+        if (!aligned(ws, 16)) return fail(DIRAC_EINVAL, "misaligned workspace");
+        if (ws_bytes < 2 * b) return fail(DIRAC_EWORKSPACE, "workspace smaller than two link fields");
+        if (overlap(U, b, ws, 2 * b) || overlap(gV, b, ws, 2 * b) || overlap(gU, b, ws, 2 * b))
+            return fail(DIRAC_EINVAL, "workspace overlaps an argument");
+    }
+    rc = launch_stout_backward(nc, g, U, gV, gU, rho, ws, as_stream(stream));
     if (rc) return fail(rc, "stout backward launch rejected");
     DIRAC_HIP(hipGetLastError());
     return DIRAC_OK;
+}
+
+int dirac_stout_backward(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,
+                         void* stream) {
+    return stout_backward(U, gV, gU, rho, nc, dims, false, nullptr, 0, stream);
+}
+
+int dirac_stout_backward_ws(const void* U, const void* gV, void* gU, double rho, int nc, const dirac_dims* dims,
+                            void* workspace, size_t ws_bytes, void* stream) {
+    return stout_backward(U, gV, gU, rho, nc, dims, true, workspace, ws_bytes, stream);
 }
 
 int dirac_brillouin_links_backward(const void* V, const void* gW, void* gV, int nc, const dirac_dims* dims,

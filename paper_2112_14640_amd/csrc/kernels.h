@@ -64,7 +64,9 @@ int launch_force(dirac_op op, int nc, int nv, const Geom& g, const void* U, cons
                  void* gout, double coeff, hipStream_t st);
 int launch_project_su(int nc, int64_t nlinks, const void* U, const void* g, void* F, hipStream_t st);
 int launch_stout(int nc, const Geom& g, const void* U, void* V, double rho, hipStream_t st);
-int launch_stout_backward(int nc, const Geom& g, const void* U, const void* gV, void* gU, double rho, hipStream_t st);
+// ws: two link fields (8 nc^2 complex128 per site), or null (the neighbours' parts are then added with atomics)
+int launch_stout_backward(int nc, const Geom& g, const void* U, const void* gV, void* gU, double rho, void* ws,
+                          hipStream_t st);
 int launch_links_backward(int nc, const Geom& g, const void* V, const void* gW, void* gV, hipStream_t st);
 
 // RHS-per-thread choice for a stencil (tunable; divides the columns the kernel sees) and kernel variant.

@@ -24,272 +24,386 @@ struct CM {
     cx<double> e[N][N];
 };
 
-template <int N>
-__device__ __forceinline__ CM<N> zero() {
-    CM<N> r;
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int j = 0; j < N; ++j) r.e[i][j] = {0.0, 0.0};
-    return r;
-}
+// The kernels of a smearing step give a link N_c threads: thread i owns row i of every matrix, so that a product
+// row x matrix needs no exchange and only the right factor is held whole.  Rows meet in LDS where a whole matrix or
+// an adjoint's row is needed.  A work-group takes kStoutLinks links.
+constexpr int kStoutLinks = 64;
 
 template <int N>
-__device__ __forceinline__ CM<N> ident() {
-    CM<N> r = zero<N>();
-#pragma unroll
-    for (int i = 0; i < N; ++i) r.e[i][i] = {1.0, 0.0};
-    return r;
-}
+struct Row {
+    cx<double> e[N];
+};
 
+// r m
 template <int N>
-__device__ __forceinline__ CM<N> mul(const CM<N>& a, const CM<N>& b) {
-    CM<N> r;
+__device__ __forceinline__ Row<N> mul(const Row<N>& r, const CM<N>& m) {
+    Row<N> o;
 #pragma unroll
-    for (int i = 0; i < N; ++i)
+    for (int j = 0; j < N; ++j) {
+        cx<double> s{0.0, 0.0};
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            cx<double> s{0.0, 0.0};
-#pragma unroll
-            for (int k = 0; k < N; ++k) cfma(s, a.e[i][k], b.e[k][j]);
-            r.e[i][j] = s;
-        }
-    return r;
-}
-
-template <int N>
-__device__ __forceinline__ CM<N> adj(const CM<N>& a) {
-    CM<N> r;
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int j = 0; j < N; ++j) r.e[i][j] = cconj(a.e[j][i]);
-    return r;
-}
-
-template <int N>
-__device__ __forceinline__ void add_to(CM<N>& a, const CM<N>& b) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int j = 0; j < N; ++j) a.e[i][j] = cadd(a.e[i][j], b.e[i][j]);
-}
-
-template <int N>
-__device__ __forceinline__ CM<N> scaled(const CM<N>& a, cx<double> s) {
-    CM<N> r;
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int j = 0; j < N; ++j) r.e[i][j] = cmul(s, a.e[i][j]);
-    return r;
-}
-
-// exp(A) by scaling and squaring: A / 2^s with ||A / 2^s||_1 <= 1/4 (s from `norm_of`, so that a
-// block whose off-diagonal part enters linearly can be scaled by its diagonal blocks alone), then an
-// 18-term Taylor series, then s squarings.
-template <int N>
-__device__ CM<N> expm(const CM<N>& A, double norm_of) {
-    int s = 0;
-    double nrm = norm_of;
-    while (nrm > 0.25 && s < 40) {
-        nrm *= 0.5;
-        ++s;
+        for (int k = 0; k < N; ++k) cfma(s, r.e[k], m.e[k][j]);
+        o.e[j] = s;
     }
-    const double sc = ldexp(1.0, -s);
-    const CM<N> X = scaled(A, cx<double>{sc, 0.0});
-    CM<N> term = ident<N>(), sum = ident<N>();
-    for (int k = 1; k <= 18; ++k) {
-        term = scaled(mul(term, X), cx<double>{1.0 / k, 0.0});
-        add_to(sum, term);
-    }
-    for (int i = 0; i < s; ++i) sum = mul(sum, sum);
-    return sum;
+    return o;
 }
 
-// max column sum of |entries| of the leading n x n block
+// r m^+
 template <int N>
-__device__ __forceinline__ double norm1(const CM<N>& a, int n) {
+__device__ __forceinline__ Row<N> mul_adj(const Row<N>& r, const CM<N>& m) {
+    Row<N> o;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        cx<double> s{0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < N; ++k) cfma_conj(s, m.e[j][k], r.e[k]);
+        o.e[j] = s;
+    }
+    return o;
+}
+
+template <int N>
+__device__ __forceinline__ void add_to(Row<N>& a, const Row<N>& b) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) a.e[j] = cadd(a.e[j], b.e[j]);
+}
+
+template <int N>
+__device__ __forceinline__ Row<N> scaled(const Row<N>& a, double s) {
+    Row<N> r;
+#pragma unroll
+    for (int j = 0; j < N; ++j) r.e[j] = cscale(s, a.e[j]);
+    return r;
+}
+
+// Whole matrix, row i and row i of the adjoint of a stored N x N block (of the links, or of rows met in LDS)
+template <int N, typename E>
+__device__ __forceinline__ CM<N> whole(const E* p) {
+    CM<N> m;
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+        for (int b = 0; b < N; ++b) m.e[a][b] = {p[a * N + b].x, p[a * N + b].y};
+    return m;
+}
+template <int N, typename E>
+__device__ __forceinline__ Row<N> row_of(const E* p, int i) {
+    Row<N> r;
+#pragma unroll
+    for (int j = 0; j < N; ++j) r.e[j] = {p[i * N + j].x, p[i * N + j].y};
+    return r;
+}
+template <int N, typename E>
+__device__ __forceinline__ Row<N> adj_row_of(const E* p, int i) {
+    Row<N> r;
+#pragma unroll
+    for (int j = 0; j < N; ++j) r.e[j] = {p[j * N + i].x, -p[j * N + i].y};
+    return r;
+}
+template <int N>
+__device__ __forceinline__ void put_row(double2* p, int i, const Row<N>& r) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) p[i * N + j] = make_double2(r.e[j].re, r.e[j].im);
+}
+
+template <int NC>
+__device__ __forceinline__ void atomic_add_row(double2* __restrict__ G, int64_t site, int mu, int i, const Row<NC>& r) {
+    double* p = reinterpret_cast<double*>(G + ((site * 4 + mu) * NC + i) * NC);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        atomicAdd(p + 2 * j, r.e[j].re);
+        atomicAdd(p + 2 * j + 1, r.e[j].im);
+    }
+}
+
+__device__ __forceinline__ int64_t shifted(const Coord& c, int mu, int s, const Geom& g) {
+    return site_index(wrap(c.x + (mu == 0 ? s : 0), g.nx), wrap(c.y + (mu == 1 ? s : 0), g.ny),
+                      wrap(c.z + (mu == 2 ? s : 0), g.nz), wrap(c.t + (mu == 3 ? s : 0), g.nt), g);
+}
+
+__device__ __forceinline__ int64_t shifted2(const Coord& c, int mu, int s, int nu, int t, const Geom& g) {
+    return site_index(wrap(c.x + (mu == 0 ? s : (nu == 0 ? t : 0)), g.nx),
+                      wrap(c.y + (mu == 1 ? s : (nu == 1 ? t : 0)), g.ny),
+                      wrap(c.z + (mu == 2 ? s : (nu == 2 ? t : 0)), g.nz),
+                      wrap(c.t + (mu == 3 ? s : (nu == 3 ? t : 0)), g.nt), g);
+}
+
+// One thread's place: row i of the link (site, mu).  Threads past the last link shadow it without storing (they
+// take part in the barriers).
+struct LinkRow {
+    int64_t site;
+    int mu, i, slot;  // slot: the link's place in the work-group
+    bool active;
+    Coord c;
+};
+template <int NC>
+__device__ __forceinline__ LinkRow link_row(const Geom& g) {
+    LinkRow l;
+    l.slot = static_cast<int>(threadIdx.x) / NC;
+    l.i = static_cast<int>(threadIdx.x) - l.slot * NC;
+    int64_t link = static_cast<int64_t>(blockIdx.x) * kStoutLinks + l.slot;
+    l.active = link < 4 * g.vol;
+    if (!l.active) link = 4 * g.vol - 1;
+    l.site = link >> 2;
+    l.mu = static_cast<int>(link & 3);
+    l.c = site_coord(l.site, g);
+    return l;
+}
+
+// Row i of C_mu(n) / rho: the six staples
+template <int NC>
+__device__ __forceinline__ Row<NC> staple_row(const double2* __restrict__ U, const LinkRow& l, const Geom& g) {
+    constexpr int L = NC * NC;
+    Row<NC> acc;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) acc.e[j] = {0.0, 0.0};
+    const int64_t n_mu = shifted(l.c, l.mu, 1, g);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int nu = k + (k >= l.mu);
+        const int64_t n_nu = shifted(l.c, nu, 1, g), m_nu = shifted(l.c, nu, -1, g);
+        const int64_t m_nu_p_mu = shifted2(l.c, nu, -1, l.mu, 1, g);
+        const Row<NC> up = mul(row_of<NC>(U + (l.site * 4 + nu) * L, l.i), whole<NC>(U + (n_nu * 4 + l.mu) * L));
+        add_to(acc, mul_adj(up, whole<NC>(U + (n_mu * 4 + nu) * L)));
+        const Row<NC> dn = mul(adj_row_of<NC>(U + (m_nu * 4 + nu) * L, l.i), whole<NC>(U + (m_nu * 4 + l.mu) * L));
+        add_to(acc, mul(dn, whole<NC>(U + (m_nu_p_mu * 4 + nu) * L)));
+    }
+    return acc;
+}
+
+// Row i of half the traceless anti-hermitian part of a matrix met in LDS, with the sign of the adjoint:
+// (A - Tr A / N) / 2 with A = M - M^+
+template <int NC>
+__device__ __forceinline__ Row<NC> traceless_row(const double2* m, int i) {
+    const Row<NC> r = row_of<NC>(m, i), d = adj_row_of<NC>(m, i);
+    double tr = 0.0;  // the trace of M - M^+ is 2 i tr
+#pragma unroll
+    for (int k = 0; k < NC; ++k) tr += m[k * NC + k].y;
+    Row<NC> o;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        o.e[j] = cscale(0.5, csub(r.e[j], d.e[j]));
+        if (j == i) o.e[j].im -= tr / NC;
+    }
+    return o;
+}
+
+// max column sum of |entries|
+template <int N>
+__device__ __forceinline__ double norm1(const CM<N>& a) {
     double m = 0.0;
-    for (int j = 0; j < n; ++j) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
         double c = 0.0;
-        for (int i = 0; i < n; ++i) c += fabs(a.e[i][j].re) + fabs(a.e[i][j].im);
+#pragma unroll
+        for (int i = 0; i < N; ++i) c += fabs(a.e[i][j].re) + fabs(a.e[i][j].im);
         m = c > m ? c : m;
     }
     return m;
 }
 
-template <int NC>
-__device__ __forceinline__ CM<NC> load_link(const double2* __restrict__ U, int64_t site, int mu) {
-    CM<NC> m;
-    const double2* p = U + (site * 4 + mu) * NC * NC;
+// Rows of E = exp(A) and, with FRECHET, of D = L(A, G), the upper right block of exp([[A, G], [0, A]]), by scaling
+// and squaring: A and G over 2^s with ||A / 2^s||_1 <= 1/4, a Taylor series of both (T_k = T_{k-1} A / k,
+// D_k = (D_{k-1} A + T_{k-1} G) / k; at 1/4 its 14 terms leave 1e-21), then s times E <- E E, D <- E D + D E.
+// Carrying the two blocks instead of the 2N x 2N matrix is a quarter of its products.  e, d: LDS for the rows of
+// the work-group's links; the squarings of the work-group are counted in `squarings` (LDS, zero on entry).
+constexpr int kExpTerms = 14;
+template <int NC, bool FRECHET>
+__device__ __forceinline__ void exp_rows(CM<NC> A, CM<NC> G, int i, double2* e, double2* d, int* squarings, Row<NC>& E,
+                                         Row<NC>& D) {
+    int s = 0;
+    for (double nrm = norm1(A); nrm > 0.25 && s < 40; nrm *= 0.5) ++s;
+    const double sc = ldexp(1.0, -s);
 #pragma unroll
     for (int a = 0; a < NC; ++a)
 #pragma unroll
         for (int b = 0; b < NC; ++b) {
-            const double2 v = p[a * NC + b];
-            m.e[a][b] = {v.x, v.y};
+            A.e[a][b] = cscale(sc, A.e[a][b]);
+            if constexpr (FRECHET) G.e[a][b] = cscale(sc, G.e[a][b]);
         }
-    return m;
-}
-
-template <int NC>
-__device__ __forceinline__ void atomic_add_link(double2* __restrict__ G, int64_t site, int mu, const CM<NC>& m) {
-    double* p = reinterpret_cast<double*>(G + (site * 4 + mu) * NC * NC);
+    Row<NC> T, Dk;
 #pragma unroll
-    for (int a = 0; a < NC; ++a)
-#pragma unroll
-        for (int b = 0; b < NC; ++b) {
-            atomicAdd(p + 2 * (a * NC + b), m.e[a][b].re);
-            atomicAdd(p + 2 * (a * NC + b) + 1, m.e[a][b].im);
-        }
-}
-
-__device__ __forceinline__ int64_t shifted(const Coord& c, int mu, int s, const Geom& g) {
-    int x[4] = {c.x, c.y, c.z, c.t};
-    const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
-    x[mu] = wrap(x[mu] + s, ext[mu]);
-    return site_index(x[0], x[1], x[2], x[3], g);
-}
-
-__device__ __forceinline__ int64_t shifted2(const Coord& c, int mu, int s, int nu, int t, const Geom& g) {
-    int x[4] = {c.x, c.y, c.z, c.t};
-    const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
-    x[mu] = wrap(x[mu] + s, ext[mu]);
-    x[nu] = wrap(x[nu] + t, ext[nu]);
-    return site_index(x[0], x[1], x[2], x[3], g);
-}
-
-// C_mu(n) / rho: the six staples
-template <int NC>
-__device__ CM<NC> staple_sum(const double2* __restrict__ U, int64_t site, const Coord& c, int mu, const Geom& g) {
-    CM<NC> acc = zero<NC>();
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        const int64_t n_nu = shifted(c, nu, 1, g), n_mu = shifted(c, mu, 1, g);
-        add_to(acc, mul(mul(load_link<NC>(U, site, nu), load_link<NC>(U, n_nu, mu)), adj(load_link<NC>(U, n_mu, nu))));
-        const int64_t m_nu = shifted(c, nu, -1, g), m_nu_p_mu = shifted2(c, nu, -1, mu, 1, g);
-        add_to(acc, mul(mul(adj(load_link<NC>(U, m_nu, nu)), load_link<NC>(U, m_nu, mu)), load_link<NC>(U, m_nu_p_mu, nu)));
+    for (int j = 0; j < NC; ++j) {
+        T.e[j] = E.e[j] = {j == i ? 1.0 : 0.0, 0.0};
+        Dk.e[j] = D.e[j] = {0.0, 0.0};
     }
-    return acc;
+#pragma unroll 1
+    for (int k = 1; k <= kExpTerms; ++k) {
+        const double inv = 1.0 / k;
+        if constexpr (FRECHET) {
+            Dk = mul(Dk, A);
+            add_to(Dk, mul(T, G));
+            Dk = scaled(Dk, inv);
+            add_to(D, Dk);
+        }
+        T = scaled(mul(T, A), inv);
+        add_to(E, T);
+    }
+    atomicMax(squarings, s);
+    __syncthreads();
+    const int most = *squarings;
+    for (int q = 0; q < most; ++q) {
+        put_row<NC>(e, i, E);
+        if constexpr (FRECHET) put_row<NC>(d, i, D);
+        __syncthreads();
+        if (q < s) {
+            const CM<NC> W = whole<NC>(e);
+            if constexpr (FRECHET) {
+                D = mul(D, W);
+                add_to(D, mul(E, whole<NC>(d)));
+            }
+            E = mul(E, W);
+        }
+        __syncthreads();
+    }
 }
 
-// X = i Q for the link (mu, n): Q = (i/2)(Omega^+ - Omega) minus its trace, Omega = C U^+
+// V = exp(i Q) U for every link.  i Q = -(A - Tr A / N) / 2 with A = Omega^+ - Omega.
 template <int NC>
-__device__ __forceinline__ CM<NC> stout_x(const CM<NC>& C, const CM<NC>& Ul) {
-    const CM<NC> om = mul(C, adj(Ul));
-    CM<NC> a;  // Omega^+ - Omega (anti-hermitian)
-#pragma unroll
-    for (int i = 0; i < NC; ++i)
-#pragma unroll
-        for (int j = 0; j < NC; ++j) a.e[i][j] = csub(cconj(om.e[j][i]), om.e[i][j]);
-    cx<double> tr{0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < NC; ++i) tr = cadd(tr, a.e[i][i]);
-#pragma unroll
-    for (int i = 0; i < NC; ++i) a.e[i][i] = csub(a.e[i][i], cscale(1.0 / NC, tr));
-    // X = i Q = i (i/2) a = -a/2
-    return scaled(a, cx<double>{-0.5, 0.0});
+__global__ __launch_bounds__(kStoutLinks * NC) void stout_kernel(const double2* __restrict__ U, double2* __restrict__ V,
+                                                                 double rho, Geom g) {
+    constexpr int L = NC * NC;
+    __shared__ double2 m0[kStoutLinks][L], m1[kStoutLinks][L];
+    __shared__ int squarings;
+    if (threadIdx.x == 0) squarings = 0;
+    const LinkRow l = link_row<NC>(g);
+    double2* const b0 = m0[l.slot];
+    double2* const b1 = m1[l.slot];
+    const double2* up = U + (l.site * 4 + l.mu) * L;
+    const Row<NC> C = scaled(staple_row<NC>(U, l, g), rho);
+    put_row<NC>(b0, l.i, mul_adj(C, whole<NC>(up)));  // Omega
+    __syncthreads();
+    put_row<NC>(b1, l.i, traceless_row<NC>(b0, l.i));  // i Q
+    __syncthreads();
+    const CM<NC> X = whole<NC>(b1);
+    Row<NC> E, D;
+    exp_rows<NC, false>(X, X, l.i, b0, b1, &squarings, E, D);
+    if (l.active) put_row<NC>(V + (l.site * 4 + l.mu) * L, l.i, mul(E, whole<NC>(up)));
 }
 
-template <int NC>
-__global__ __launch_bounds__(128) void stout_kernel(const double2* __restrict__ U, double2* __restrict__ V, double rho,
-                                                    Geom g) {
-    const int64_t gid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (gid >= 4 * g.vol) return;
-    const int64_t site = gid >> 2;
-    const int mu = static_cast<int>(gid & 3);
-    const Coord c = site_coord(site, g);
-    const CM<NC> C = scaled(staple_sum<NC>(U, site, c, mu, g), cx<double>{rho, 0.0});
-    const CM<NC> Ul = load_link<NC>(U, site, mu);
-    const CM<NC> X = stout_x(C, Ul);
-    const CM<NC> Vl = mul(expm(X, norm1(X, NC)), Ul);
-    double2* out = V + (site * 4 + mu) * NC * NC;
-#pragma unroll
-    for (int a = 0; a < NC; ++a)
-#pragma unroll
-        for (int b = 0; b < NC; ++b) out[a * NC + b] = make_double2(Vl.e[a][b].re, Vl.e[a][b].im);
-}
-
-// gU += the gradient with respect to U of L(U'(U)) given gV = dL/dU' (one stout step)
-template <int NC>
-__global__ __launch_bounds__(64) void stout_backward_kernel(const double2* __restrict__ U,
-                                                            const double2* __restrict__ GV,
-                                                            double2* __restrict__ GU, double rho, Geom g) {
-    const int64_t gid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (gid >= 4 * g.vol) return;
-    const int64_t site = gid >> 2;
-    const int mu = static_cast<int>(gid & 3);
-    const Coord c = site_coord(site, g);
-    const CM<NC> C = scaled(staple_sum<NC>(U, site, c, mu, g), cx<double>{rho, 0.0});
-    const CM<NC> Ul = load_link<NC>(U, site, mu);
-    const CM<NC> X = stout_x(C, Ul);
-    const double nx = norm1(X, NC);
-    const CM<NC> E = expm(X, nx);
-    const CM<NC> Gv = load_link<NC>(GV, site, mu);
-    // V = E U: direct part E^+ G_V, and G_E = G_V U^+
-    CM<NC> gu = mul(adj(E), Gv);
-    const CM<NC> GE = mul(Gv, adj(Ul));
-    // G_X = L(X^+, G_E) from the block exponential
-    constexpr int N2 = 2 * NC;
-    CM<N2> M = zero<N2>();
-    const CM<NC> Xd = adj(X);
-#pragma unroll
-    for (int i = 0; i < NC; ++i)
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            M.e[i][j] = Xd.e[i][j];
-            M.e[NC + i][NC + j] = Xd.e[i][j];
-            M.e[i][NC + j] = GE.e[i][j];
+// gU += the gradient with respect to U of L(U'(U)) given gV = dL/dU' (one stout step).  A link passes the gradient of
+// its staple products, G_P, on to the 18 links of its staples.  With a workspace (SCATTER false) the link's own part
+// and G_P are stored there, two link fields, and stout_gather_kernel collects the 18 parts of every link; without,
+// they are added with atomics, 19 matrices a link, which the atomic rate bounds (28 G/s: 437 us at 8^3 x 16 with
+// N_c = 3, 587 with a thread per link and the 2N x 2N exponential in scratch memory; gathered: 27 + 40 us).
+template <int NC, bool SCATTER>
+__global__ __launch_bounds__(kStoutLinks * NC) void stout_backward_kernel(const double2* __restrict__ U,
+                                                                          const double2* __restrict__ GV,
+                                                                          double2* __restrict__ GU,
+                                                                          double2* __restrict__ ws, double rho, Geom g) {
+    constexpr int L = NC * NC;
+    __shared__ double2 m0[kStoutLinks][L], m1[kStoutLinks][L], m2[kStoutLinks][L];
+    __shared__ int squarings;
+    if (threadIdx.x == 0) squarings = 0;
+    const LinkRow l = link_row<NC>(g);
+    double2* const b0 = m0[l.slot];
+    double2* const b1 = m1[l.slot];
+    double2* const b2 = m2[l.slot];
+    const double2* up = U + (l.site * 4 + l.mu) * L;
+    const double2* gvp = GV + (l.site * 4 + l.mu) * L;
+    Row<NC> gu;
+    {
+        const Row<NC> C = scaled(staple_row<NC>(U, l, g), rho);
+        put_row<NC>(b1, l.i, C);
+        const CM<NC> Ul = whole<NC>(up);
+        put_row<NC>(b0, l.i, mul_adj(C, Ul));                           // Omega
+        put_row<NC>(b2, l.i, mul_adj(row_of<NC>(gvp, l.i), Ul));       // V = E U: G_E = G_V U^+
+    }
+    __syncthreads();
+    Row<NC> E, GX;
+    {
+        // X = i Q is anti-hermitian: A = X^+ = -X, and exp(A) = E^+
+        const Row<NC> A = scaled(traceless_row<NC>(b0, l.i), -1.0);
+        const CM<NC> GE = whole<NC>(b2);
+        __syncthreads();
+        put_row<NC>(b0, l.i, A);
+        __syncthreads();
+        const CM<NC> Am = whole<NC>(b0);
+        __syncthreads();
+        exp_rows<NC, true>(Am, GE, l.i, b0, b2, &squarings, E, GX);  // G_X = L(X^+, G_E)
+    }
+    gu = mul(E, whole<NC>(gvp));  // direct part E^+ G_V
+    put_row<NC>(b0, l.i, GX);
+    __syncthreads();
+    // X = i Q -> G_Q = -i G_X; Q = (i/2) A - (i/2N) Tr A -> G_A = -(1/2)(G_X - Tr(G_X)/N) with A = Om^+ - Om ->
+    // G_Om = G_A^+ - G_A: the traceless anti-hermitian part of G_X
+    const Row<NC> GOm = traceless_row<NC>(b0, l.i);
+    // Omega = C U^+: U gains G_Om^+ C = -G_Om C, and G_C = G_Om U
+    add_to(gu, scaled(mul(GOm, whole<NC>(b1)), -1.0));
+    const Row<NC> gp = scaled(mul(GOm, whole<NC>(up)), rho);  // gradient of every staple product
+    if constexpr (!SCATTER) {
+        if (l.active) {
+            put_row<NC>(ws + (l.site * 4 + l.mu) * L, l.i, gp);
+            put_row<NC>(ws + ((g.vol + l.site) * 4 + l.mu) * L, l.i, gu);
         }
-    const CM<N2> EM = expm(M, nx);
-    CM<NC> GX;
-#pragma unroll
-    for (int i = 0; i < NC; ++i)
-#pragma unroll
-        for (int j = 0; j < NC; ++j) GX.e[i][j] = EM.e[i][NC + j];
-    // X = i Q -> G_Q = -i G_X; Q = (i/2) A - (i/2N) Tr A -> G_A = (-i/2)(G_Q - Tr(G_Q)/N); A = Om^+ - Om ->
-    // G_Om = G_A^+ - G_A; with G_Q = -i G_X: G_A = -(1/2)(G_X - Tr(G_X)/N)
-    CM<NC> GA;
-    cx<double> trx{0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < NC; ++i) trx = cadd(trx, GX.e[i][i]);
-#pragma unroll
-    for (int i = 0; i < NC; ++i)
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            cx<double> v = GX.e[i][j];
-            if (i == j) v = csub(v, cscale(1.0 / NC, trx));
-            GA.e[i][j] = cscale(-0.5, v);
+        return;
+    }
+    put_row<NC>(b2, l.i, gp);
+    if (l.active) atomic_add_row<NC>(GU, l.site, l.mu, l.i, gu);
+    __syncthreads();
+    if (!l.active) return;
+    const CM<NC> GP = whole<NC>(b2);
+    const Row<NC> gpd = adj_row_of<NC>(b2, l.i);
+    const int mu = l.mu, i = l.i;
+    const int64_t n_mu = shifted(l.c, mu, 1, g);
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        const int nu = k + (k >= mu);
+        {  // A B D^+ = U_nu(n) U_mu(n+nu) U_nu(n+mu)^+
+            const int64_t n_nu = shifted(l.c, nu, 1, g);
+            const double2 *a = U + (l.site * 4 + nu) * L, *b = U + (n_nu * 4 + mu) * L, *d = U + (n_mu * 4 + nu) * L;
+            const CM<NC> B = whole<NC>(b), D = whole<NC>(d);
+            atomic_add_row<NC>(GU, l.site, nu, i, mul_adj(mul(gp, D), B));              // G (B D^+)^+
+            atomic_add_row<NC>(GU, n_nu, mu, i, mul(mul(adj_row_of<NC>(a, i), GP), D));  // A^+ G D
+            atomic_add_row<NC>(GU, n_mu, nu, i, mul(mul(gpd, whole<NC>(a)), B));         // G^+ A B
         }
-    CM<NC> GOm;
-#pragma unroll
-    for (int i = 0; i < NC; ++i)
-#pragma unroll
-        for (int j = 0; j < NC; ++j) GOm.e[i][j] = csub(cconj(GA.e[j][i]), GA.e[i][j]);
-    // Omega = C U^+: G_C = G_Om U, and U gains G_Om^+ C
-    add_to(gu, mul(adj(GOm), C));
-    atomic_add_link<NC>(GU, site, mu, gu);
-    const CM<NC> GP = scaled(mul(GOm, Ul), cx<double>{rho, 0.0});  // gradient of every staple product
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        {  // A B D = U_nu(n) U_mu(n+nu) U_nu(n+mu)^+
-            const int64_t n_nu = shifted(c, nu, 1, g), n_mu = shifted(c, mu, 1, g);
-            const CM<NC> A = load_link<NC>(U, site, nu), B = load_link<NC>(U, n_nu, mu),
-                         D = adj(load_link<NC>(U, n_mu, nu));
-            atomic_add_link<NC>(GU, site, nu, mul(GP, adj(mul(B, D))));
-            atomic_add_link<NC>(GU, n_nu, mu, mul(mul(adj(A), GP), adj(D)));
-            atomic_add_link<NC>(GU, n_mu, nu, adj(mul(adj(mul(A, B)), GP)));  // D = U^+: gradient daggered
-        }
-        {  // A B D = U_nu(n-nu)^+ U_mu(n-nu) U_nu(n-nu+mu)
-            const int64_t m_nu = shifted(c, nu, -1, g), m_nu_p_mu = shifted2(c, nu, -1, mu, 1, g);
-            const CM<NC> A = adj(load_link<NC>(U, m_nu, nu)), B = load_link<NC>(U, m_nu, mu),
-                         D = load_link<NC>(U, m_nu_p_mu, nu);
-            atomic_add_link<NC>(GU, m_nu, nu, adj(mul(GP, adj(mul(B, D)))));  // A = U^+
-            atomic_add_link<NC>(GU, m_nu, mu, mul(mul(adj(A), GP), adj(D)));
-            atomic_add_link<NC>(GU, m_nu_p_mu, nu, mul(adj(mul(A, B)), GP));
+        {  // A^+ B D = U_nu(n-nu)^+ U_mu(n-nu) U_nu(n-nu+mu)
+            const int64_t m_nu = shifted(l.c, nu, -1, g), m_nu_p_mu = shifted2(l.c, nu, -1, mu, 1, g);
+            const double2 *a = U + (m_nu * 4 + nu) * L, *b = U + (m_nu * 4 + mu) * L, *d = U + (m_nu_p_mu * 4 + nu) * L;
+            const CM<NC> A = whole<NC>(a), D = whole<NC>(d);
+            const Row<NC> bd = mul(row_of<NC>(b, i), D);
+            atomic_add_row<NC>(GU, m_nu, nu, i, mul_adj(bd, GP));                       // B D G^+
+            atomic_add_row<NC>(GU, m_nu, mu, i, mul_adj(mul(row_of<NC>(a, i), GP), D));  // A G D^+
+            atomic_add_row<NC>(GU, m_nu_p_mu, nu, i, mul(mul(adj_row_of<NC>(b, i), A), GP));  // B^+ A G
         }
     }
+}
+
+// gU of the link (nu, m) from the workspace of stout_backward_kernel: its own part and, for each other axis la, its
+// six places in the staples of other links, G the staple gradient of the link at the site and direction given:
+//   staples of links along la:  G(m) U_nu(m+la) U_la(m+nu)^+,  G(m-la)^+ U_nu(m-la) U_la(m-la+nu),
+//                               U_la(m) U_nu(m+la) G(m+nu)^+,  U_la(m-la)^+ U_nu(m-la) G(m-la+nu);
+//   staples of links along nu:  U_la(m-la)^+ G(m-la) U_la(m-la+nu),  U_la(m) G(m+la) U_la(m+nu)^+.
+template <int NC>
+__global__ __launch_bounds__(kStoutLinks * NC) __attribute__((amdgpu_waves_per_eu(NC <= 3 ? 2 : 1))) void stout_gather_kernel(const double2* __restrict__ U,
+                                                                        const double2* __restrict__ ws,
+                                                                        double2* __restrict__ GU, Geom g) {
+    constexpr int L = NC * NC;
+    const LinkRow l = link_row<NC>(g);
+    if (!l.active) return;
+    const int nu = l.mu, i = l.i;
+    Row<NC> acc = row_of<NC>(ws + ((g.vol + l.site) * 4 + nu) * L, i);
+    const int64_t m_nu = shifted(l.c, nu, 1, g);
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        const int la = k + (k >= nu);
+        const int64_t p = shifted(l.c, la, 1, g), q = shifted(l.c, la, -1, g), q_nu = shifted2(l.c, la, -1, nu, 1, g);
+        const double2 *ula = U + (l.site * 4 + la) * L, *ula_q = U + (q * 4 + la) * L;
+        {
+            const CM<NC> u = whole<NC>(U + (p * 4 + nu) * L);
+            add_to(acc, mul_adj(mul(row_of<NC>(ws + (l.site * 4 + la) * L, i), u), whole<NC>(U + (m_nu * 4 + la) * L)));
+            add_to(acc, mul_adj(mul(row_of<NC>(ula, i), u), whole<NC>(ws + (m_nu * 4 + la) * L)));
+        }
+        {
+            const CM<NC> u = whole<NC>(U + (q * 4 + nu) * L);
+            add_to(acc, mul(mul(adj_row_of<NC>(ula_q, i), u), whole<NC>(ws + (q_nu * 4 + la) * L)));
+            const CM<NC> v = whole<NC>(U + (q_nu * 4 + la) * L);
+            add_to(acc, mul(mul(adj_row_of<NC>(ws + (q * 4 + la) * L, i), u), v));
+            add_to(acc, mul(mul(adj_row_of<NC>(ula_q, i), whole<NC>(ws + (q * 4 + nu) * L)), v));
+        }
+        add_to(acc, mul_adj(mul(row_of<NC>(ula, i), whole<NC>(ws + (p * 4 + nu) * L)), whole<NC>(U + (m_nu * 4 + la) * L)));
+    }
+    atomic_add_row<NC>(GU, l.site, nu, i, acc);  // one add per element; atomic, so calls on two streams may share gU
 }
 
 // ---------------------------------------------------------------------------
@@ -526,18 +640,23 @@ __global__ __launch_bounds__(kSplitSites * kSplitGroups * NC) void links_backwar
 }
 
 template <int NC>
-int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out, double rho, hipStream_t st) {
+int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out, double rho, hipStream_t st,
+              void* ws) {
     auto A = static_cast<const double2*>(a);
     auto B = static_cast<const double2*>(b);
     auto O = static_cast<double2*>(out);
     if (which == 0) {
-        const int block = 128;
-        hipLaunchKernelGGL((stout_kernel<NC>), dim3(static_cast<unsigned>((4 * g.vol + block - 1) / block)),
-                           dim3(block), 0, st, A, O, rho, g);
+        hipLaunchKernelGGL((stout_kernel<NC>), dim3(static_cast<unsigned>((4 * g.vol + kStoutLinks - 1) / kStoutLinks)),
+                           dim3(kStoutLinks * NC), 0, st, A, O, rho, g);
     } else if (which == 1) {
-        const int block = 64;
-        hipLaunchKernelGGL((stout_backward_kernel<NC>), dim3(static_cast<unsigned>((4 * g.vol + block - 1) / block)),
-                           dim3(block), 0, st, A, B, O, rho, g);
+        const dim3 grid(static_cast<unsigned>((4 * g.vol + kStoutLinks - 1) / kStoutLinks)), block(kStoutLinks * NC);
+        auto w = static_cast<double2*>(ws);
+        if (w) {
+            hipLaunchKernelGGL((stout_backward_kernel<NC, false>), grid, block, 0, st, A, B, O, w, rho, g);
+            hipLaunchKernelGGL((stout_gather_kernel<NC>), grid, block, 0, st, A, w, O, g);
+        } else {
+            hipLaunchKernelGGL((stout_backward_kernel<NC, true>), grid, block, 0, st, A, B, O, w, rho, g);
+        }
     } else {
         const int64_t blocks = (g.vol + kSplitSites - 1) / kSplitSites * 4;
         hipLaunchKernelGGL((links_backward_kernel<NC>), dim3(static_cast<unsigned>(grid_blocks_x8(blocks, 1))),
@@ -546,12 +665,13 @@ int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out,
     return DIRAC_OK;
 }
 
-int dispatch(int which, int nc, const Geom& g, const void* a, const void* b, void* out, double rho, hipStream_t st) {
+int dispatch(int which, int nc, const Geom& g, const void* a, const void* b, void* out, double rho, hipStream_t st,
+             void* ws = nullptr) {
     switch (nc) {
-        case 1: return launch_nc<1>(which, g, a, b, out, rho, st);
-        case 2: return launch_nc<2>(which, g, a, b, out, rho, st);
-        case 3: return launch_nc<3>(which, g, a, b, out, rho, st);
-        case 4: return launch_nc<4>(which, g, a, b, out, rho, st);
+        case 1: return launch_nc<1>(which, g, a, b, out, rho, st, ws);
+        case 2: return launch_nc<2>(which, g, a, b, out, rho, st, ws);
+        case 3: return launch_nc<3>(which, g, a, b, out, rho, st, ws);
+        case 4: return launch_nc<4>(which, g, a, b, out, rho, st, ws);
     }
     return DIRAC_EUNSUPPORTED;
 }
@@ -562,8 +682,9 @@ int launch_stout(int nc, const Geom& g, const void* U, void* V, double rho, hipS
     return dispatch(0, nc, g, U, nullptr, V, rho, st);
 }
 
-int launch_stout_backward(int nc, const Geom& g, const void* U, const void* gV, void* gU, double rho, hipStream_t st) {
-    return dispatch(1, nc, g, U, gV, gU, rho, st);
+int launch_stout_backward(int nc, const Geom& g, const void* U, const void* gV, void* gU, double rho, void* ws,
+                          hipStream_t st) {
+    return dispatch(1, nc, g, U, gV, gU, rho, st, ws);
 }
 
 int launch_links_backward(int nc, const Geom& g, const void* V, const void* gW, void* gV, hipStream_t st) {

@@ -289,8 +289,15 @@ def stout_backward(U, gV, rho, out=None):
     _require_like(gV, "gV", U)
     out = torch.zeros_like(U) if out is None else out
     _require_like(out, "out", U)
-    L.check(L.load().dirac_stout_backward(_ptr(U), _ptr(gV), _ptr(out), float(rho), nc, C.byref(d), _stream()),
-            "dirac_stout_backward")
+    lib = L.load()
+    try:  # two link fields, so that the neighbours' parts are gathered; without room for them they are added in place
+        ws = torch.empty((2, *U.shape), dtype=U.dtype, device=U.device)
+    except torch.OutOfMemoryError:
+        L.check(lib.dirac_stout_backward(_ptr(U), _ptr(gV), _ptr(out), float(rho), nc, C.byref(d), _stream()),
+                "dirac_stout_backward")
+        return out
+    L.check(lib.dirac_stout_backward_ws(_ptr(U), _ptr(gV), _ptr(out), float(rho), nc, C.byref(d), _ptr(ws),
+                                        ws.numel() * 16, _stream()), "dirac_stout_backward_ws")
     return out
 
 

@@ -7,6 +7,8 @@ oracle (FP64).
 * end to end, U -> stout -> V -> W -> D_B u (and through a CG solve on D_B^+ D_B) by torch.autograd over
   the library's backward kernels, against central differences of the oracle chain.
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -17,6 +19,7 @@ from oracle.dense import brillouin_dense
 from oracle.brillouin import brillouin_links_all
 from oracle.stout import stout_smear, stout_step
 from paper_2112_14640_amd import autograd as ag
+from paper_2112_14640_amd import _lib as L
 from paper_2112_14640_amd import dirac
 from tests.gpu_helpers import host, to_dev
 
@@ -58,6 +61,30 @@ def test_stout_backward_against_differences(nc):
         E = _cg(np.random.default_rng(620 + k), U.shape)
         want = _fd(lambda u: float(np.sum(np.conj(R) * stout_step(u, rho)).real), U, E)
         assert abs(_rdot(gU, E) - want) < 1e-7 * max(1.0, abs(want)), (k, _rdot(gU, E), want)
+
+
+@pytest.mark.parametrize("nc,dims", [(1, (3, 2, 5, 3)), (2, (3, 3, 3, 5)), (3, (5, 3, 3, 3)), (4, (2, 3, 2, 3)),
+                                     (3, (2, 2, 2, 2))])
+@pytest.mark.parametrize("rho", [0.12, 2.5])
+def test_stout_step_ragged_groups(nc, dims, rho):
+    """Every colour count, link counts that leave the last work-group partly empty, wrapping extents of 2, and with
+    rho = 2.5 arguments that take several squarings, differing from link to link: the forward step element by element,
+    the backward against central differences and its two forms (gathered, added with atomics) against each other."""
+    rng = np.random.default_rng(670 + nc)
+    U = si.gauge_field(rng, dims, nc, "haar")
+    R, base, E = (_cg(rng, U.shape) for _ in range(3))
+    assert np.max(np.abs(host(dirac.stout_step(to_dev(U), rho)) - stout_step(U, rho))) < (1e-13 if rho < 1 else 1e-11)
+    Ud, Rd = to_dev(U), to_dev(R)
+    gU = host(dirac.stout_backward(Ud, Rd, rho, out=to_dev(base))) - base
+    want = _fd(lambda u: float(np.sum(np.conj(R) * stout_step(u, rho)).real), U, E)
+    assert abs(_rdot(gU, E) - want) < (1e-7 if rho < 1 else 1e-5) * max(1.0, abs(want))
+    out = to_dev(base)
+    d = L.Dims()
+    for k, n in enumerate(dims):
+        d.n[k] = n
+    L.check(L.load().dirac_stout_backward(Ud.data_ptr(), Rd.data_ptr(), out.data_ptr(), rho, nc, C.byref(d),
+                                          torch.cuda.current_stream().cuda_stream), "dirac_stout_backward")
+    assert np.max(np.abs(host(out) - base - gU)) < 1e-13 * max(1.0, np.max(np.abs(gU)))
 
 
 @pytest.mark.parametrize("nc", [2, 3])
