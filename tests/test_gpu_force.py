@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import synthetic_inputs as si
+from oracle.brillouin import brillouin_apply
 from oracle.dense import wilson_dense
 from oracle.force import project_su, staggered_force, wilson_force
 from oracle.wilson import wilson_apply
@@ -27,6 +28,35 @@ def test_force_matches_oracle(op, apbc):
     assert np.max(np.abs(g - ref)) < 1e-12 * np.max(np.abs(ref))
     g2 = host(dirac.force(op, to_dev(U), to_dev(psi), to_dev(chi), -2.5, apbc, out=to_dev(g)))
     np.testing.assert_allclose(g2, -1.5 * ref, atol=1e-12)
+
+
+@pytest.mark.parametrize("op,dims", [("wilson", (3, 5, 2, 3)), ("staggered", (2, 4, 6, 2)), ("wilson", (2, 2, 2, 2))])
+@pytest.mark.parametrize("nc,nv", [(1, 1), (2, 2), (3, 3), (3, 4), (3, 5), (3, 12), (4, 9)])
+def test_force_lane_splits(op, dims, nc, nv):
+    """One, two and four right-hand sides at a time with remainders, every colour count, site counts that leave the
+    last work-group partly empty, and an output that is added to."""
+    rng = np.random.default_rng(25 + nv)
+    U = si.gauge_field(rng, dims, nc, "haar")
+    mk = si.staggered_vector if op == "staggered" else si.wilson_vector
+    psi, chi = mk(rng, dims, nc, nv), mk(rng, dims, nc, nv)
+    base = si.complex_gaussian(rng, U.shape)
+    ref = (staggered_force if op == "staggered" else wilson_force)(U, psi, chi, True)
+    g = host(dirac.force(op, to_dev(U), to_dev(psi), to_dev(chi), 0.5, True, out=to_dev(base)))
+    assert np.max(np.abs(g - base - 0.5 * ref)) < 1e-13 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("dims,nc,nv", [((3, 2, 3, 2), 1, 1), ((2, 3, 2, 3), 2, 2), ((3, 3, 2, 3), 3, 5), ((2, 2, 2, 3), 4, 4)])
+def test_brillouin_force_lane_splits(dims, nc, nv):
+    """The Brillouin link gradient against the bilinear it differentiates, which is linear in W (and adjoint in the
+    directions that are not stored): Re sum conj(g) E is the change of Re psi^+ D_B(W) chi for W -> W + E."""
+    rng = np.random.default_rng(26 + nv)
+    shape = dims[::-1] + (40, nc, nc)
+    W, E = si.complex_gaussian(rng, shape), si.complex_gaussian(rng, shape)
+    psi, chi = si.wilson_vector(rng, dims, nc, nv), si.wilson_vector(rng, dims, nc, nv)
+    g = host(dirac.force("brillouin", to_dev(W), to_dev(psi), to_dev(chi)))
+    bilinear = lambda w: float(np.sum(np.conj(psi) * brillouin_apply(w, chi, 0.1)).real)
+    want = bilinear(W + E) - bilinear(W)
+    assert abs(float(np.sum(np.conj(g) * E).real) - want) < 1e-11 * (abs(want) + abs(bilinear(W)))
 
 
 def test_project_su_matches_oracle():
