@@ -2,7 +2,10 @@
 // buffer loads that copy whole x-rows of the lattice into LDS.
 #pragma once
 
+#include <mutex>
+#include <set>
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "kernels.h"
@@ -190,12 +193,21 @@ inline int choose_tile_rows(int, int64_t rows, int nx, int units, int nrg, uint3
     return 0;
 }
 
-// Opt a row kernel in to more than 64 KiB of dynamic LDS (once per kernel); false if refused.
-template <typename K>
-bool allow_lds(K kernel, size_t lds) {
+// Opt a row kernel in to more than 64 KiB of dynamic LDS (all the device has; once per kernel and device); false if
+// refused.
+inline bool allow_lds(const void* kernel, size_t lds) {
     if (lds <= 64 * 1024) return true;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               static_cast<int>(kRowLdsCap)) == hipSuccess;
+    static std::mutex mu;
+    static std::set<std::pair<int, const void*>> done;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lock(mu);
+    if (done.count({dev, kernel})) return true;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(max_lds_per_block())) != hipSuccess)
+        return false;
+    done.insert({dev, kernel});
+    return true;
 }
 
 // ---------------------------------------------------------------------------

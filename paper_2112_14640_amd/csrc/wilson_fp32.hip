@@ -1,0 +1,7 @@
+#include "wilson_kernels.h"
+
+namespace dirac {
+
+int launch_wilson_fp32(const StencilArgs& a, hipStream_t st) { return launch_prec<PrecF32>(a, st); }
+
+}  // namespace dirac

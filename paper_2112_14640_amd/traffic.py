@@ -37,7 +37,7 @@ import re
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = 512 * 2 ** 20
 SOURCES = {
-    "wilson": "paper_2112_14640_amd/csrc/wilson.hip",
+    "wilson": "paper_2112_14640_amd/csrc/wilson_kernels.h",
     "staggered": "paper_2112_14640_amd/csrc/staggered.hip",
     "brillouin": "paper_2112_14640_amd/csrc/brillouin.hip",
 }
