@@ -76,14 +76,6 @@ __device__ __forceinline__ float bf16_to_float(uint16_t h) {
     return __uint_as_float(static_cast<uint32_t>(h) << 16);
 }
 
-// Round to nearest, ties to even; NaN stays a quiet NaN.
-__device__ __forceinline__ uint16_t float_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu) != 0u) return static_cast<uint16_t>((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return static_cast<uint16_t>(u >> 16);
-}
-
 // Load/store of one complex element of storage type S into/out of compute type R.
 template <typename R, typename S>
 struct io;
@@ -110,9 +102,13 @@ struct io<float, bf16x2> {
         uint32_t w = *reinterpret_cast<const uint32_t*>(p);
         return {__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u)};
     }
+    // one v_cvt_pk_bf16_f32: round to nearest, ties to even, NaN stays a quiet NaN (in software it was 8
+    // instructions per real number, a tenth of the Wilson kernel's)
     __device__ static __forceinline__ void st(bf16x2* p, cx<float> v) {
-        uint32_t w = static_cast<uint32_t>(float_to_bf16(v.re)) | (static_cast<uint32_t>(float_to_bf16(v.im)) << 16);
-        *reinterpret_cast<uint32_t*>(p) = w;
+        using f32x2 = float __attribute__((ext_vector_type(2)));
+        using b16x2 = __bf16 __attribute__((ext_vector_type(2)));
+        const b16x2 w = __builtin_convertvector(f32x2{v.re, v.im}, b16x2);
+        *reinterpret_cast<uint32_t*>(p) = __builtin_bit_cast(uint32_t, w);
     }
 };
 // Conversions used by casts and mixed-precision BLAS (double accumulate).

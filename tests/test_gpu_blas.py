@@ -117,3 +117,20 @@ def test_measurement_probes():
     assert torch.equal(b, a)
     with pytest.raises(ValueError):
         measure.row_gather_rate((6, 4, 6, 6), site_bytes, a, b)  # nz not a multiple of 4
+
+
+def test_cast_to_bf16_rounds_like_torch():
+    """Ties, overflow to infinity, subnormals, signed zeros and NaN, and a sweep of exponents, bit for bit."""
+    special = np.array([0x00000000, 0x80000000, 0x3f808000, 0x3f818000, 0x3f807fff, 0x3f808001, 0x7f7fffff, 0xff7f8000,
+                        0x7f7f7fff, 0x7f800000, 0xff800000, 0x00000001, 0x00008000, 0x00018000, 0x007fffff, 0x80400000],
+                       dtype=np.uint32)
+    rng = np.random.default_rng(31)
+    bits = np.concatenate([special, rng.integers(0, 1 << 32, 8176, dtype=np.uint32)])
+    f = bits.view(np.float32)
+    f = np.where(np.isnan(f), np.float32(1.5), f)
+    x = torch.from_numpy(f.view(np.complex64).reshape(-1, 4)).to("cuda:0")
+    y = dirac.cast(x, "bf16").view(torch.int16).cpu()
+    ref = torch.view_as_real(x).cpu().to(torch.bfloat16).view(torch.int16)
+    assert torch.equal(y, ref)
+    nan = dirac.cast(torch.full((1, 4), complex(float("nan"), 1.0), dtype=torch.complex64, device="cuda:0"), "bf16")
+    assert torch.isnan(nan[..., 0]).all() and (nan[..., 1] == 1).all()
