@@ -61,24 +61,37 @@ __device__ __forceinline__ const double* spin_table<double>(int dag, int flip, i
 // sites in LDS (slot = direction number; in the output precision, products accumulated in
 // FP64), and writes each site's 40 stored directions as one contiguous block.
 // ---------------------------------------------------------------------------
-struct LevelDirs {
-    unsigned char dir[64];  // level 2 (24 directions), level 3 (32), level 4 stored (8)
+// A task is one direction of one site.  Its last steps are listed in a packed table (order-templated loops, no
+// branch on the direction) and the sites it reads come from a table of offsets in LDS: with the steps as branches and
+// the neighbour's index divided out per step, three quarters of the kernel's instructions were neither products nor
+// conversions (0.60 ms at 16^3 x 32 in FP32, N_c = 3; now 0.30, bound by the address rate of the link loads: loading a
+// wavefront's 64 matrices together, consecutive lanes consecutive elements, was slower, 0.52 ms, the exchange through
+// LDS costing more than the addresses).
+struct LevelTable {
+    // bits 0-6 the direction; for its k-th last step, from bit 8 + 10 k: 7 bits the direction one step shorter, 2 bits
+    // the axis, 1 bit whether the step is forwards.  Level 2 (24 directions), level 3 (32), level 4 stored (8)
+    uint64_t task[64];
 };
-constexpr LevelDirs make_level_dirs() {
-    LevelDirs l{};
+constexpr int kDirStride[4] = {1, 3, 9, 27};
+constexpr LevelTable make_level_table() {
+    LevelTable l{};
     int n = 0;
     for (int k = 2; k <= 4; ++k)
         for (int dir = 0; dir < 81; ++dir) {
             int nz = 0;
-            for (int mu = 0, q = dir; mu < 4; ++mu, q /= 3) nz += q % 3 != 1;
-            if (nz == k && (k < 4 || dir < 40)) l.dir[n++] = static_cast<unsigned char>(dir);
+            uint64_t t = static_cast<uint64_t>(dir);
+            for (int mu = 0, q = dir; mu < 4; ++mu, q /= 3) {
+                const int s = q % 3 - 1;
+                if (s == 0) continue;
+                const uint64_t prev = static_cast<uint64_t>(dir - s * kDirStride[mu]);
+                t |= (prev | static_cast<uint64_t>(mu) << 7 | static_cast<uint64_t>(s > 0) << 9) << (8 + 10 * nz);
+                ++nz;
+            }
+            if (nz == k && (k < 4 || dir < 40)) l.task[n++] = t;
         }
     return l;
 }
-__constant__ LevelDirs c_levels = make_level_dirs();
-constexpr int kLevelStart[3] = {0, 24, 56};
-constexpr int kLevelCount[3] = {24, 32, 8};
-constexpr int kDirStride[4] = {1, 3, 9, 27};
+__constant__ LevelTable c_levels = make_level_table();
 
 template <int NC>
 constexpr int link_tile_sites() {
@@ -92,51 +105,48 @@ __global__ __launch_bounds__(kLinkThreads) void links_kernel(const GI* __restric
     constexpr int L = NC * NC;
     using T = std::conditional_t<sizeof(GO) == 8, float, double>;
     __shared__ cx<T> lw[S][81][L];
+    __shared__ int disp[S][81];  // site offset of each displacement (32 bits: V < 2^31)
     const int64_t site0 = logical_block() * S;
     if (site0 >= g.vol) return;
     const int ns = static_cast<int>(g.vol - site0 < S ? g.vol - site0 : S);
     const int tid = threadIdx.x;
-    const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
-    auto link_at = [&](const int* c, int mu) __attribute__((always_inline)) {
-        return U + (site_index(c[0], c[1], c[2], c[3], g) * 4 + mu) * L;
-    };
+    __shared__ Coord at[S];
+    if (tid < S) at[tid] = site_coord(site0 + (tid < ns ? tid : 0), g);
+    __syncthreads();
+    for (int u = tid; u < S * 81; u += kLinkThreads) {
+        const int s = u / 81, d = u % 81;
+        const Coord c = at[s];
+        disp[s][d] = static_cast<int>(site_index(wrap(c.x + d % 3 - 1, g.nx), wrap(c.y + (d / 3) % 3 - 1, g.ny),
+                                                 wrap(c.z + (d / 9) % 3 - 1, g.nz), wrap(c.t + d / 27 - 1, g.nt), g) -
+                                      site0);
+    }
+    __syncthreads();
     // level 1: W_{+e_mu}(n) = V_mu(n), W_{-e_mu}(n) = V_mu(n - e_mu)^+
     for (int u = tid; u < ns * 8 * L; u += kLinkThreads) {
         const int s = u / (8 * L), j = (u / L) % 8, e = u % L;
         const int mu = j >> 1, a = e / NC, b = e % NC;
-        const Coord c0 = site_coord(site0 + s, g);
-        int c[4] = {c0.x, c0.y, c0.z, c0.t};
-        if (j & 1) {
-            c[mu] = wrap(c[mu] - 1, ext[mu]);
-            lw[s][40 - kDirStride[mu]][e] = cconj(io<T, GI>::ld(link_at(c, mu) + b * NC + a));
-        } else {
-            lw[s][40 + kDirStride[mu]][e] = io<T, GI>::ld(link_at(c, mu) + e);
-        }
+        const int stride = mu == 0 ? 1 : (mu == 1 ? 3 : (mu == 2 ? 9 : 27));
+        const int dir = (j & 1) ? 40 - stride : 40 + stride;
+        const GI* l = U + ((site0 + disp[s][(j & 1) ? dir : 40]) * 4 + mu) * L;
+        const cx<T> v = io<T, GI>::ld(l + ((j & 1) ? b * NC + a : e));
+        lw[s][dir][e] = (j & 1) ? cconj(v) : v;
     }
     __syncthreads();
-#pragma unroll 1
-    for (int lev = 0; lev < 3; ++lev) {
-        const int k = lev + 2, cnt = kLevelCount[lev];
-        const double inv = 1.0 / k;
-        for (int u = tid; u < ns * cnt; u += kLinkThreads) {
-            const int s = u / cnt;
-            const int dir = c_levels.dir[kLevelStart[lev] + (u - s * cnt)];
-            const Coord c0 = site_coord(site0 + s, g);
-            const int n0[4] = {c0.x, c0.y, c0.z, c0.t};
-            int d[4];
-            for (int mu = 0, q = dir; mu < 4; ++mu, q /= 3) d[mu] = q % 3 - 1;
+    auto level = [&](auto order_c) __attribute__((always_inline)) {
+        constexpr int K = decltype(order_c)::value;
+        constexpr int FIRST = K == 2 ? 0 : (K == 3 ? 24 : 56), CNT = K == 2 ? 24 : (K == 3 ? 32 : 8);
+        for (int u = tid; u < ns * CNT; u += kLinkThreads) {
+            const int s = u / CNT;
+            const uint64_t task = c_levels.task[FIRST + u % CNT];
+            const int dir = static_cast<int>(task) & 127;
             // the links of all last steps are loaded before any product, so their latencies overlap
-            GI raw[4][L];
+            GI raw[K][L];
 #pragma unroll
-            for (int mu = 0; mu < 4; ++mu) {
-                if (d[mu] == 0) continue;
-                int c[4];
+            for (int k = 0; k < K; ++k) {
+                const uint32_t st = static_cast<uint32_t>(task >> (8 + 10 * k)) & 1023u;
+                const GI* lp = U + ((site0 + disp[s][(st >> 9) ? (st & 127u) : dir]) * 4 + ((st >> 7) & 3u)) * L;
 #pragma unroll
-                for (int nu = 0; nu < 4; ++nu)
-                    c[nu] = wrap(n0[nu] + d[nu] - (nu == mu && d[mu] > 0 ? 1 : 0), ext[nu]);
-                const GI* lp = link_at(c, mu);
-#pragma unroll
-                for (int e = 0; e < L; ++e) raw[mu][e] = lp[e];
+                for (int e = 0; e < L; ++e) raw[k][e] = lp[e];
             }
             cx<double> acc[NC][NC];
 #pragma unroll
@@ -144,20 +154,19 @@ __global__ __launch_bounds__(kLinkThreads) void links_kernel(const GI* __restric
 #pragma unroll
                 for (int b = 0; b < NC; ++b) acc[a][b] = {0.0, 0.0};
 #pragma unroll
-            for (int mu = 0; mu < 4; ++mu) {
-                if (d[mu] == 0) continue;
-                const int sg = d[mu];
-                const cx<T>* prev = lw[s][dir - sg * kDirStride[mu]];
+            for (int k = 0; k < K; ++k) {
+                const uint32_t st = static_cast<uint32_t>(task >> (8 + 10 * k)) & 1023u;
+                const bool fwd = st >> 9;
+                const cx<T>* prev = lw[s][st & 127u];
                 cx<double> l[NC][NC];
 #pragma unroll
                 for (int a = 0; a < NC; ++a)
 #pragma unroll
-                    for (int b = 0; b < NC; ++b) {
-                        const cx<double> v = io<double, GI>::ld(&raw[mu][a * NC + b]);
-                        if (sg > 0)
-                            l[a][b] = v;
-                        else
-                            l[b][a] = cconj(v);
+                    for (int b = 0; b < NC; ++b) {  // L, or its adjoint for a backward step
+                        GI v = raw[k][a * NC + b];
+                        if (!fwd) v = raw[k][b * NC + a];
+                        if (!fwd) v.y = -v.y;
+                        l[a][b] = io<double, GI>::ld(&v);
                     }
 #pragma unroll
                 for (int a = 0; a < NC; ++a)
@@ -172,12 +181,15 @@ __global__ __launch_bounds__(kLinkThreads) void links_kernel(const GI* __restric
             for (int a = 0; a < NC; ++a)
 #pragma unroll
                 for (int b = 0; b < NC; ++b) {
-                    const cx<double> v = cscale(inv, acc[a][b]);
+                    const cx<double> v = cscale(1.0 / K, acc[a][b]);
                     lw[s][dir][a * NC + b] = {static_cast<T>(v.re), static_cast<T>(v.im)};
                 }
         }
         __syncthreads();
-    }
+    };
+    level(std::integral_constant<int, 2>{});
+    level(std::integral_constant<int, 3>{});
+    level(std::integral_constant<int, 4>{});
     // the stored directions 0..39 of the tile's sites are one contiguous block of W
     GO* out = W + site0 * 40 * L;
     for (int u = tid; u < ns * 40 * L; u += kLinkThreads) {

@@ -174,14 +174,16 @@ struct Coord {
     int x, y, z, t;
 };
 
+// (the library limits the volume to < 2^31 sites: 32-bit divisions)
 __device__ __forceinline__ Coord site_coord(int64_t s, const Geom& g) {
     Coord c;
-    int64_t q = s / g.nx;
-    c.x = static_cast<int>(s - q * g.nx);
-    int64_t q2 = q / g.ny;
-    c.y = static_cast<int>(q - q2 * g.ny);
-    int64_t q3 = q2 / g.nz;
-    c.z = static_cast<int>(q2 - q3 * g.nz);
+    const uint32_t q0 = static_cast<uint32_t>(s), nx = g.nx, ny = g.ny, nz = g.nz;
+    const uint32_t q = q0 / nx;
+    c.x = static_cast<int>(q0 - q * nx);
+    const uint32_t q2 = q / ny;
+    c.y = static_cast<int>(q - q2 * ny);
+    const uint32_t q3 = q2 / nz;
+    c.z = static_cast<int>(q2 - q3 * nz);
     c.t = static_cast<int>(q3);
     return c;
 }
@@ -208,19 +210,20 @@ struct SiteOrder {
 };
 
 __device__ __forceinline__ int64_t ordered_site(int64_t i, const SiteOrder& o, const Geom& g) {
-    const int64_t col = i / o.column;
-    const int64_t r = i - col * o.column;
-    const int t = static_cast<int>(r / o.bslice);
-    int q = static_cast<int>(r - static_cast<int64_t>(t) * o.bslice);
+    const uint32_t u = static_cast<uint32_t>(i), column = static_cast<uint32_t>(o.column);  // V < 2^31
+    const uint32_t col = u / column;
+    const uint32_t r = u - col * column;
+    const int t = static_cast<int>(r / static_cast<uint32_t>(o.bslice));
+    int q = static_cast<int>(r - static_cast<uint32_t>(t) * o.bslice);
     const int bxy = o.bx * o.by;
     const int lz = q / bxy;
     q -= lz * bxy;
     const int ly = q / o.bx;
     const int lx = q - ly * o.bx;
-    const int cbx = static_cast<int>(col % o.nbx);
-    const int64_t c2 = col / o.nbx;
-    const int cby = static_cast<int>(c2 % o.nby);
-    const int cbz = static_cast<int>(c2 / o.nby);
+    const int c2 = static_cast<int>(col / static_cast<uint32_t>(o.nbx));
+    const int cbx = static_cast<int>(col) - c2 * o.nbx;
+    const int cbz = c2 / o.nby;
+    const int cby = c2 - cbz * o.nby;
     return site_index(cbx * o.bx + lx, cby * o.by + ly, cbz * o.bz + lz, t, g);
 }
 

@@ -512,9 +512,12 @@ __global__ __launch_bounds__(kSplitSites * kSplitGroups * NC) void links_backwar
     const int tid = threadIdx.x;
     const int ax[3] = {trans_axis(mu, 0), trans_axis(mu, 1), trans_axis(mu, 2)};
     for (int u = tid; u < kSplitGroups * kSplitPairs; u += T) pairs[u] = c_split.pair[mu][0][u];
+    __shared__ Coord at[S];
+    if (tid < S) at[tid] = site_coord(site0 + (tid < ns ? tid : 0), g);
+    __syncthreads();
     for (int u = tid; u < S * 54; u += T) {
         const int s = u / 54, pc = u % 54, c = pc % 27;
-        const Coord c0 = site_coord(site0 + (s < ns ? s : 0), g);
+        const Coord c0 = at[s];
         int x[4] = {c0.x, c0.y, c0.z, c0.t};
         const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
 #pragma unroll
