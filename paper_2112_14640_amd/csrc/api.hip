@@ -114,6 +114,8 @@ int choose_rb(dirac_op op, dirac_prec prec, int nc, int nv, const Geom& g) {
     if (o > 0) return cols % o == 0 ? o : 1;
     switch (op) {
         case DIRAC_WILSON:
+            // two right-hand sides on rows too short for a row tile: one thread per site, its block contiguous
+            if (nv == 2 && g.nx < 32 && prec != DIRAC_FP64) return 2;
             return (static_cast<int64_t>(g.nx) * nv > 512 && nv % 2 == 0) ? 2 : 1;
         case DIRAC_STAGGERED: {
             if (cols % 2 != 0) return 1;

@@ -263,6 +263,9 @@ inline int64_t grid_blocks_x8(int64_t threads, int block) {
     return (nb + 7) / 8 * 8;
 }
 
+// Work-group size of the direct kernels: 256, or 64 where that many would not give each of the 256 CUs a work-group.
+inline int direct_block(int64_t threads) { return threads >= 256 * 256 ? 256 : 64; }
+
 // ---------------------------------------------------------------------------
 // Host-side error plumbing
 // ---------------------------------------------------------------------------

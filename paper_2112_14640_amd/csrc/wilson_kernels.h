@@ -138,89 +138,24 @@ __device__ __forceinline__ void hop_with(cx<typename P::R> (&acc)[RB][NC][4], co
     }
 }
 
-// Direction-generic hop (runtime mu and projector sign, wave-uniform).  With P = 1 + sig g_mu
-// in the chiral basis the half spinor is h0 = p0 + c0 p_A, h1 = p1 + c1 p_B and the full spinor
-// is rebuilt as (h0, h1, e2 h_C, e3 h_D), where every c, e is one of +-1, +-i:
-//   mu=0: A,B = 3,2  c0,c1 = -sig i, -sig i   C,D = 1,0  e2,e3 = sig i, sig i
-//   mu=1: A,B = 3,2  c0,c1 = -sig, +sig       C,D = 1,0  e2,e3 = sig, -sig
-//   mu=2: A,B = 2,3  c0,c1 = -sig i, +sig i   C,D = 0,1  e2,e3 = sig i, -sig i
-//   mu=3: A,B = 2,3  c0,c1 = +sig, +sig       C,D = 0,1  e2,e3 = sig, sig
-struct UnitC {
-    int re, im;
-};
-template <typename R>
-__device__ __forceinline__ cx<R> umul(UnitC u, cx<R> x) {
-    // (u.re + i u.im)(x.re + i x.im), u one of +-1, +-i
-    return {R(u.re) * x.re - R(u.im) * x.im, R(u.re) * x.im + R(u.im) * x.re};
-}
-
-template <int NC, int RB, class P>
-__device__ __forceinline__ void hop_rt(cx<typename P::R> (&acc)[RB][NC][4], const typename P::G* __restrict__ link,
-                                       bool adj, const typename P::S* __restrict__ nb, int nv, typename P::R scale,
-                                       int mu, int sig) {
-    using R = typename P::R;
-    const bool lo = mu < 2;
-    UnitC c0, c1, e2, e3;
-    switch (mu) {
-        case 0: c0 = {0, -sig}; c1 = {0, -sig}; e2 = {0, sig}; e3 = {0, sig}; break;
-        case 1: c0 = {-sig, 0}; c1 = {sig, 0}; e2 = {sig, 0}; e3 = {-sig, 0}; break;
-        case 2: c0 = {0, -sig}; c1 = {0, sig}; e2 = {0, sig}; e3 = {0, -sig}; break;
-        default: c0 = {sig, 0}; c1 = {sig, 0}; e2 = {sig, 0}; e3 = {sig, 0}; break;
-    }
-    cx<R> l[NC][NC];
-    if (adj) {
-#pragma unroll
-        for (int a = 0; a < NC; ++a)
-#pragma unroll
-            for (int b = 0; b < NC; ++b) l[b][a] = cconj(io<R, typename P::G>::ld(link + a * NC + b));
-    } else {
-#pragma unroll
-        for (int a = 0; a < NC; ++a)
-#pragma unroll
-            for (int b = 0; b < NC; ++b) l[a][b] = io<R, typename P::G>::ld(link + a * NC + b);
-    }
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-        cx<R> h0[NC], h1[NC];
-#pragma unroll
-        for (int b = 0; b < NC; ++b) {
-            cx<R> p[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) p[s] = io<R, typename P::S>::ld(nb + (b * 4 + s) * nv + k);
-            const cx<R> pa = lo ? p[3] : p[2];
-            const cx<R> pb = lo ? p[2] : p[3];
-            h0[b] = cscale(scale, cadd(p[0], umul(c0, pa)));
-            h1[b] = cscale(scale, cadd(p[1], umul(c1, pb)));
-        }
-#pragma unroll
-        for (int a = 0; a < NC; ++a) {
-            cx<R> x0{R(0), R(0)}, x1{R(0), R(0)};
-#pragma unroll
-            for (int b = 0; b < NC; ++b) {
-                cfma(x0, l[a][b], h0[b]);
-                cfma(x1, l[a][b], h1[b]);
-            }
-            acc[k][a][0] = cadd(acc[k][a][0], x0);
-            acc[k][a][1] = cadd(acc[k][a][1], x1);
-            acc[k][a][2] = cadd(acc[k][a][2], umul(e2, lo ? x1 : x0));
-            acc[k][a][3] = cadd(acc[k][a][3], umul(e3, lo ? x0 : x1));
-        }
-    }
-}
-
-// Direct form: one thread per (site, RB right-hand sides), neighbours read from global memory, one
-// hop direction per loop iteration (only its loads are live, which keeps the register count and so
-// the waves per SIMD moderate).  It serves the shapes the row tiles cannot take.
-template <int NC, int RB, bool DAG, class P>
+// Direct form: one thread per (site, RB right-hand sides), neighbours read from global memory, the two hops of an axis
+// in flight together.  It serves the shapes the row tiles cannot take: a few right-hand sides, or too few or too many
+// threads in a row.  NVC > 0 fixes N_v (= RB) at compile time: a site block is then contiguous in a thread and its loads
+// are 16 bytes wide.  Bound by the address rate of the loads: with one 8-byte load per element and one hop at a
+// time, 100 us at 22 x 18 x 14 x 30 (FP32, N_c = 3, N_v = 1) and 19 us (one work-group) at 4^4 in FP64; now RAGGED_US
+// and SMALL_US.
+template <int NC, int RB, bool DAG, class P, int NVC>
 __global__ __launch_bounds__(256) void wilson_kernel(const typename P::G* __restrict__ U,
                                                       const typename P::S* __restrict__ in,
                                                       typename P::S* __restrict__ out, typename P::R diag, Geom g,
                                                       int nv, SiteOrder order, const typename P::R* __restrict__ clov) {
     using R = typename P::R;
-    const int nrg = nv / RB;
+    constexpr int L = NC * NC;
+    if constexpr (NVC > 0) nv = NVC;
+    const int nrg = NVC > 0 ? NVC / RB : nv / RB;
     const int64_t gid = logical_block() * blockDim.x + threadIdx.x;
     if (gid >= g.vol * nrg) return;
-    const int64_t idx = gid / nrg;
+    const int64_t idx = nrg == 1 ? gid : gid / nrg;
     const int r0 = static_cast<int>(gid - idx * nrg) * RB;
     const int64_t site = ordered_site(idx, order, g);
     const Coord c = site_coord(site, g);
@@ -237,30 +172,37 @@ __global__ __launch_bounds__(256) void wilson_kernel(const typename P::G* __rest
                 acc[k][a][s] = cscale(diag, io<R, typename P::S>::ld(centre + (a * 4 + s) * nv + k));
     if (clov) clover_add<NC, RB>(acc, centre, nv, clov + site * clover_reals<NC>());
 
-    const int co[4] = {c.x, c.y, c.z, c.t};
-    const int ext[4] = {g.nx, g.ny, g.nz, g.nt};
-#pragma nounroll
-    for (int d = 0; d < 8; ++d) {
-        const int mu = d >> 1;
-        const bool back = d & 1;
-        const int64_t stride = mu == 0 ? 1 : (mu == 1 ? g.nx : (mu == 2 ? static_cast<int64_t>(g.nx) * g.ny
-                                                                         : static_cast<int64_t>(g.nx) * g.ny * g.nz));
-        const int cm = mu == 0 ? co[0] : (mu == 1 ? co[1] : (mu == 2 ? co[2] : co[3]));
-        const int em = mu == 0 ? ext[0] : (mu == 1 ? ext[1] : (mu == 2 ? ext[2] : ext[3]));
-        int64_t nbs;
-        R scale = R(-0.5);
-        if (!back) {
-            nbs = site + (cm == em - 1 ? (1 - em) * stride : stride);
-            if (mu == 3 && g.apbc && cm == em - 1) scale = R(0.5);
-        } else {
-            nbs = site - (cm == 0 ? (1 - em) * stride : stride);
-            if (mu == 3 && g.apbc && cm == 0) scale = R(0.5);
-        }
-        // D: forward (1 - g_mu), backward (1 + g_mu); the adjoint swaps them
-        const int sig = (back != DAG) ? 1 : -1;
-        const typename P::G* link = U + ((back ? nbs : site) * 4 + mu) * NC * NC;
-        hop_rt<NC, RB, P>(acc, link, back, in + nbs * vs + r0, nv, scale, mu, sig);
-    }
+    // The loads of the next hop (of the next axis, where two hops fit the registers) wait for the sums of this one: an
+    // opaque zero that depends on them goes into the addresses.  All hops in flight at once spill.
+    constexpr bool PAIR = RB * sizeof(R) <= 8;
+    int later = 0;
+    auto wait_for_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+#pragma unroll
+            for (int a = 0; a < NC; ++a)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(later), "+v"(acc[k][a][s].re), "+v"(acc[k][a][s].im));
+    };
+    auto axis = [&](auto mu_c, int x, int n, int64_t stride) __attribute__((always_inline)) {
+        constexpr int MU = decltype(mu_c)::value;
+        constexpr int SF = DAG ? 1 : -1;  // forward projector 1 + SF g_mu
+        const bool flip = MU == 3 && g.apbc;  // fermion sign of a hop across the boundary
+        const int64_t here = site + later;
+        const int64_t fwd = here + (x == n - 1 ? (1 - n) * stride : stride);
+        cx<R> l[NC][NC];
+        load_link<NC, false, P>(l, U + (here * 4 + MU) * L);
+        hop_with<NC, RB, MU, SF, P, NVC>(acc, l, in + fwd * vs + r0, nv, flip && x == n - 1 ? R(0.5) : R(-0.5));
+        if constexpr (!PAIR) wait_for_sums();
+        const int64_t bwd = site + later - (x == 0 ? (1 - n) * stride : stride);
+        load_link<NC, true, P>(l, U + (bwd * 4 + MU) * L);
+        hop_with<NC, RB, MU, -SF, P, NVC>(acc, l, in + bwd * vs + r0, nv, flip && x == 0 ? R(0.5) : R(-0.5));
+        wait_for_sums();
+    };
+    axis(std::integral_constant<int, 0>{}, c.x, g.nx, 1);
+    axis(std::integral_constant<int, 1>{}, c.y, g.ny, g.nx);
+    axis(std::integral_constant<int, 2>{}, c.z, g.nz, static_cast<int64_t>(g.nx) * g.ny);
+    axis(std::integral_constant<int, 3>{}, c.t, g.nt, static_cast<int64_t>(g.nx) * g.ny * g.nz);
 
     typename P::S* o = out + site * vs + r0;
 #pragma unroll
@@ -610,8 +552,8 @@ bool launch_rb(const StencilArgs& a, hipStream_t st) {
     if (a.variant == 4 && launch_rows<NC, RB, P>(a, st)) return true;
     if (a.epi.mode != 0) return false;
     // direct loads (selected, or the row tile does not fit this shape)
-    const int block = 256;
     const int64_t threads = a.g.vol * (a.nv / RB);
+    const int block = direct_block(threads);
     const dim3 grid(static_cast<unsigned>(grid_blocks_x8(threads, block)));
     const R diag = static_cast<R>(4.0 + a.mass);
     auto U = static_cast<const typename P::G*>(a.gauge);
@@ -619,12 +561,20 @@ bool launch_rb(const StencilArgs& a, hipStream_t st) {
     auto out = static_cast<typename P::S*>(a.out);
     auto clov = static_cast<const R*>(a.clover);
     const SiteOrder ord = make_site_order(a.g);
-    if (a.dagger)
-        hipLaunchKernelGGL((wilson_kernel<NC, RB, true, P>), grid, dim3(block), 0, st, U, in, out, diag, a.g, a.nv, ord,
-                           clov);
-    else
-        hipLaunchKernelGGL((wilson_kernel<NC, RB, false, P>), grid, dim3(block), 0, st, U, in, out, diag, a.g, a.nv,
-                           ord, clov);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(block), 0, st, U, in, out, diag, a.g, a.nv, ord, clov);
+    };
+    if (a.nv == RB) {
+        if (a.dagger)
+            go(wilson_kernel<NC, RB, true, P, RB>);
+        else
+            go(wilson_kernel<NC, RB, false, P, RB>);
+    } else {
+        if (a.dagger)
+            go(wilson_kernel<NC, RB, true, P, 0>);
+        else
+            go(wilson_kernel<NC, RB, false, P, 0>);
+    }
     return true;
 }
 
