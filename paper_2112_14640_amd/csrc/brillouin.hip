@@ -253,7 +253,8 @@ __device__ __forceinline__ void spin_accumulate(cx<R> (&o)[4], const cx<R> (&ch)
     if (hx) gamma_x_accumulate(o, ch, q1);
 }
 
-template <int NC, int RB, bool DAG, class P>
+// NVC > 0 fixes N_v (= RB) at compile time: the site block is then contiguous in a thread and loaded 16 bytes at a time.
+template <int NC, int RB, bool DAG, class P, int NVC>
 __global__ __launch_bounds__(256) void brillouin_kernel(const typename P::G* __restrict__ W,
                                                          const typename P::S* __restrict__ in,
                                                          typename P::S* __restrict__ out, typename P::R diag, Geom g,
@@ -261,10 +262,11 @@ __global__ __launch_bounds__(256) void brillouin_kernel(const typename P::G* __r
                                                          int lap) {
     using R = typename P::R;
     using S = typename P::S;
-    const int nrg = nv / RB;
+    if constexpr (NVC > 0) nv = NVC;
+    const int nrg = NVC > 0 ? NVC / RB : nv / RB;
     const int64_t gid = logical_block() * blockDim.x + threadIdx.x;
     if (gid >= g.vol * nrg) return;
-    const int64_t idx = gid / nrg;
+    const int64_t idx = nrg == 1 ? gid : gid / nrg;
     const int r0 = static_cast<int>(gid - idx * nrg) * RB;
     const int64_t site = ordered_site(idx, order, g);
     const Coord c = site_coord(site, g);
@@ -794,8 +796,8 @@ template <int NC, int RB, class P>
 void launch_rb(const StencilArgs& a, hipStream_t st) {
     using R = typename P::R;
     if (a.variant == 4 && launch_rows<NC, RB, P>(a, st)) return;
-    const int block = 256;
     const int64_t threads = a.g.vol * (a.nv / RB);
+    const int block = direct_block(threads);
     const dim3 grid(static_cast<unsigned>(grid_blocks_x8(threads, block)));
     const R diag = static_cast<R>(centre_coefficient(a));
     auto W = static_cast<const typename P::G*>(a.gauge);
@@ -803,12 +805,20 @@ void launch_rb(const StencilArgs& a, hipStream_t st) {
     auto out = static_cast<typename P::S*>(a.out);
     auto clov = static_cast<const R*>(a.clover);
     const int lap = a.laplace ? 1 : 0;
-    if (a.dagger)
-        hipLaunchKernelGGL((brillouin_kernel<NC, RB, true, P>), grid, dim3(block), 0, st, W, in, out, diag, a.g, a.nv,
-                           make_site_order(a.g), clov, lap);
-    else
-        hipLaunchKernelGGL((brillouin_kernel<NC, RB, false, P>), grid, dim3(block), 0, st, W, in, out, diag, a.g,
-                           a.nv, make_site_order(a.g), clov, lap);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(block), 0, st, W, in, out, diag, a.g, a.nv, make_site_order(a.g), clov, lap);
+    };
+    if (a.nv == RB) {
+        if (a.dagger)
+            go(brillouin_kernel<NC, RB, true, P, RB>);
+        else
+            go(brillouin_kernel<NC, RB, false, P, RB>);
+    } else {
+        if (a.dagger)
+            go(brillouin_kernel<NC, RB, true, P, 0>);
+        else
+            go(brillouin_kernel<NC, RB, false, P, 0>);
+    }
 }
 
 template <int NC, class P>

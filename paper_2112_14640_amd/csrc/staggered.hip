@@ -48,16 +48,19 @@ __device__ __forceinline__ void stag_hop(cx<typename P::R> (&acc)[RB][NC], const
     }
 }
 
-template <int NC, int RB, bool DAG, class P>
+// NVC > 0 fixes the columns (= RB) at compile time: the site block is then contiguous in a thread and loaded 16 bytes at
+// a time.
+template <int NC, int RB, bool DAG, class P, int NVC>
 __global__ __launch_bounds__(256) void staggered_kernel(const typename P::G* __restrict__ U,
                                                          const typename P::S* __restrict__ in,
                                                          typename P::S* __restrict__ out, typename P::R mass, Geom g,
                                                          int nv, SiteOrder order, int lap) {
     using R = typename P::R;
-    const int nrg = nv / RB;
+    if constexpr (NVC > 0) nv = NVC;
+    const int nrg = NVC > 0 ? NVC / RB : nv / RB;
     const int64_t gid = logical_block() * blockDim.x + threadIdx.x;
     if (gid >= g.vol * nrg) return;
-    const int64_t idx = gid / nrg;
+    const int64_t idx = nrg == 1 ? gid : gid / nrg;
     const int r0 = static_cast<int>(gid - idx * nrg) * RB;
     const int64_t site = ordered_site(idx, order, g);
     const Coord c = site_coord(site, g);
@@ -373,20 +376,28 @@ bool launch_rb(const StencilArgs& a, hipStream_t st) {
     const R diag = static_cast<R>(a.laplace ? 4.0 + 0.5 * a.mass * a.mass : a.mass);
     if (a.variant == 4 && launch_rows<NC, RB, P>(a, nv, diag, st)) return true;
     if (a.epi.mode != 0) return false;
-    const int block = 256;
     const int64_t threads = a.g.vol * (nv / RB);
+    const int block = direct_block(threads);
     const dim3 grid(static_cast<unsigned>(grid_blocks_x8(threads, block)));
     auto U = static_cast<const typename P::G*>(a.gauge);
     auto in = static_cast<const typename P::S*>(a.in);
     auto out = static_cast<typename P::S*>(a.out);
     const SiteOrder ord = make_site_order(a.g);
     const int lap = a.laplace ? 1 : 0;
-    if (a.dagger)
-        hipLaunchKernelGGL((staggered_kernel<NC, RB, true, P>), grid, dim3(block), 0, st, U, in, out, diag, a.g, nv,
-                           ord, lap);
-    else
-        hipLaunchKernelGGL((staggered_kernel<NC, RB, false, P>), grid, dim3(block), 0, st, U, in, out, diag, a.g, nv,
-                           ord, lap);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(block), 0, st, U, in, out, diag, a.g, nv, ord, lap);
+    };
+    if (nv == RB) {
+        if (a.dagger)
+            go(staggered_kernel<NC, RB, true, P, RB>);
+        else
+            go(staggered_kernel<NC, RB, false, P, RB>);
+    } else {
+        if (a.dagger)
+            go(staggered_kernel<NC, RB, true, P, 0>);
+        else
+            go(staggered_kernel<NC, RB, false, P, 0>);
+    }
     return true;
 }
 

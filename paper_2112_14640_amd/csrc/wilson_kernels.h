@@ -142,8 +142,8 @@ __device__ __forceinline__ void hop_with(cx<typename P::R> (&acc)[RB][NC][4], co
 // in flight together.  It serves the shapes the row tiles cannot take: a few right-hand sides, or too few or too many
 // threads in a row.  NVC > 0 fixes N_v (= RB) at compile time: a site block is then contiguous in a thread and its loads
 // are 16 bytes wide.  Bound by the address rate of the loads: with one 8-byte load per element and one hop at a
-// time, 100 us at 22 x 18 x 14 x 30 (FP32, N_c = 3, N_v = 1) and 19 us (one work-group) at 4^4 in FP64; now RAGGED_US
-// and SMALL_US.
+// time, 100 us at 22 x 18 x 14 x 30 (FP32, N_c = 3, N_v = 1), 1.22 ms at 32^3 x 64 and 19 us (one work-group) at 4^4 in
+// FP64; now 46 us, 0.58 ms and less than the 11 us that the call costs the host.
 template <int NC, int RB, bool DAG, class P, int NVC>
 __global__ __launch_bounds__(256) void wilson_kernel(const typename P::G* __restrict__ U,
                                                       const typename P::S* __restrict__ in,
