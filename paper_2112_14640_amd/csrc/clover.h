@@ -57,4 +57,30 @@ __device__ __forceinline__ void clover_add(cx<R> (&acc)[RB][NC][4], const S* __r
     }
 }
 
+// The same for one chirality: acc[a][s] += (C psi)[a][2 h + s], psi at the block's first spin (colours `colour` apart,
+// spins nv), b at the record of its block.
+template <int NC, typename R, typename S>
+__device__ __forceinline__ void clover_add_half(cx<R> (&acc)[NC][2], const S* __restrict__ psi, int colour, int nv,
+                                                const R* __restrict__ b) {
+    constexpr int N = 2 * NC;
+    cx<R> v[N], o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v[i] = io<R, S>::ld(psi + (i % NC) * colour + (i / NC) * nv);
+        o[i] = cscale(b[i], v[i]);
+    }
+    int e = N;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = i + 1; j < N; ++j) {
+            const cx<R> bij{b[e], b[e + 1]};
+            e += 2;
+            cfma(o[i], bij, v[j]);
+            cfma_conj(o[j], bij, v[i]);
+        }
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i % NC][i / NC] = cadd(acc[i % NC][i / NC], o[i]);
+}
+
 }  // namespace dirac

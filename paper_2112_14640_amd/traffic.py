@@ -39,7 +39,7 @@ COPY_BYTES = 512 * 2 ** 20
 SOURCES = {
     "wilson": "paper_2112_14640_amd/csrc/wilson_kernels.h",
     "staggered": "paper_2112_14640_amd/csrc/staggered.hip",
-    "brillouin": "paper_2112_14640_amd/csrc/brillouin.hip",
+    "brillouin": "paper_2112_14640_amd/csrc/brillouin_kernels.h",
 }
 COMMON = ["paper_2112_14640_amd/csrc/common.h", "paper_2112_14640_amd/csrc/tile.h",
           "paper_2112_14640_amd/csrc/kernels.h", "paper_2112_14640_amd/csrc/api.hip"]

@@ -338,6 +338,51 @@ STAGGERED_ROW_CASES = [
 ]
 
 
+# (dims, nc, nv): a thread per chirality and colour row (small launches), whole rows, segments with a halo whose last one
+# overlaps, and fewer than 64 threads; then launches large enough for the other forms: several window entries per lane,
+# FP64's chirality threads on whole rows and on overlapping segments
+BRILLOUIN_THREAD_CASES = [
+    ((8, 2, 3, 2), 3, 4), ((22, 2, 2, 3), 3, 12), ((8, 2, 2, 2), 3, 1), ((5, 3, 2, 2), 2, 13), ((6, 2, 3, 2), 4, 12),
+    ((16, 2, 2, 2), 1, 2), ((7, 2, 2, 3), 4, 5), ((4, 2, 2, 2), 3, 3),
+    ((16, 9, 12, 10), 3, 4), ((22, 5, 5, 5), 3, 12), ((11, 9, 8, 9), 3, 7), ((16, 8, 8, 9), 2, 12),
+]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("case", range(len(BRILLOUIN_THREAD_CASES)))
+def test_brillouin_thread_forms(case, prec):
+    dims, nc, nv = BRILLOUIN_THREAD_CASES[case]
+    gauge, u = _inputs("brillouin", dims, nc, nv, seed=540 + case)
+    dagger = case % 2 == 1
+    v, g_in, u_in = _run("brillouin", prec, gauge, u, 0.05, True, dagger)
+    parity(v, ORACLE[("brillouin", dagger)](g_in, u_in, 0.05, True), TOL[prec], (prec, dims, nc, nv))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("op,dims,nc,nv", [("wilson", (5, 3, 2, 3), 3, 1), ("wilson", (3, 4, 2, 2), 3, 2),
+                                           ("wilson", (7, 3, 3, 2), 2, 1), ("wilson", (3, 2, 5, 2), 4, 2),
+                                           ("wilson", (3, 2, 2, 3), 1, 3), ("staggered", (4, 2, 6, 2), 3, 1),
+                                           ("staggered", (2, 4, 2, 2), 4, 2), ("brillouin", (3, 2, 3, 2), 3, 1)])
+def test_direct_kernels_few_rhs(op, dims, nc, nv, prec):
+    """Shapes below a row tile: site blocks contiguous in a thread (N_v = 1 and 2) and strided."""
+    gauge, u = _inputs(op, dims, nc, nv, seed=560 + nv)
+    for dagger in (False, True):
+        v, g_in, u_in = _run(op, prec, gauge, u, 0.05, True, dagger)
+        parity(v, ORACLE[(op, dagger)](g_in, u_in, 0.05, True), TOL[prec], (op, prec, dims, nc, nv, dagger))
+
+
+# (dims, nc, nv) of the Wilson row form: links staged in LDS with N_v known only at run time, with one and with two
+# right-hand sides per thread, and rows whose staged links need more than 64 KiB of LDS
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("dims,nc,nv", [((16, 2, 2, 3), 3, 4), ((11, 3, 2, 2), 2, 7), ((24, 2, 2, 2), 3, 24),
+                                        ((32, 2, 2, 2), 3, 12), ((9, 2, 3, 2), 4, 8)])
+def test_wilson_staged_links(dims, nc, nv, prec):
+    gauge, u = _inputs("wilson", dims, nc, nv, seed=580 + nv)
+    for dagger in (False, True):
+        v, g_in, u_in = _run("wilson", prec, gauge, u, 0.05, True, dagger)
+        parity(v, ORACLE[("wilson", dagger)](g_in, u_in, 0.05, True), TOL[prec], (prec, dims, nc, nv, dagger))
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("case", range(len(STAGGERED_ROW_CASES)))
 def test_staggered_row_tiles(case, prec):
