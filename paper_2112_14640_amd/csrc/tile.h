@@ -2,6 +2,7 @@
 // buffer loads that copy whole x-rows of the lattice into LDS.
 #pragma once
 
+#include <atomic>
 #include <mutex>
 #include <set>
 #include <type_traits>
@@ -174,10 +175,12 @@ inline bool row_order_magic(const Geom& g, RowTile& rt) {
 // LDS a work-group may request on the current device (64 KiB unless the device reports more;
 // above 64 KiB a kernel must opt in with hipFuncAttributeMaxDynamicSharedMemorySize).
 inline size_t max_lds_per_block() {
+    static std::atomic<int> known[64];  // per device, 0: not asked yet
     int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v < 65536)
-        return 65536;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 65536;
+    if ((v = known[dev].load(std::memory_order_relaxed)) != 0) return static_cast<size_t>(v);
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v < 65536) v = 65536;
+    known[dev].store(v, std::memory_order_relaxed);
     return static_cast<size_t>(v);
 }
 

@@ -64,7 +64,9 @@ def _ptr(t: torch.Tensor) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of torch's current stream (on the current device), without the Stream object that
+    torch.cuda.current_stream() builds: 0.2 instead of 2.7 us of an 11 us call."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _require(t: torch.Tensor, name: str, device=None):
