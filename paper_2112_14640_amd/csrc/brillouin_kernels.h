@@ -232,17 +232,19 @@ __host__ __device__ inline uint32_t ss_pad(int nv) {
 // arithmetic and neighbour reads in twice the wavefronts, with half the sums and row copy registers each.  At one
 // thread per (site, RHS), two waves per SIMD and a work-group of three, the vector unit was busy a third of the time: 1.95 ms at 16^3 x 32 (N_c = 3, N_v = 12), now 1.51, the vector unit 57 % and LDS 55 % busy.
 //
-// PF: the next row copy is in flight during the arithmetic.  At three waves per SIMD SS has no registers for it (spilling,
-// 16^3 x 32 took 4 ms); the other work-groups of the CU cover the copies instead.  Where the launch would not fill two waves
-// per SIMD, SS with PF gives every colour row a thread as well, N_c times the wavefronts with an N_c-th of the work
-// (8^3 x 16, N_v = 4: 58 us in FP64, 74 without; FP32 takes it there too, 44 us, 100 in
-// the direct kernel).
+// At three waves per SIMD SS alone has no registers for a row copy in flight during the arithmetic (spilling, 16^3 x 32
+// took 4 ms); the other work-groups of the CU cover the copies instead.
+//
+// CS: every colour row has a thread of its own, N_c times the wavefronts with an N_c-th of the work each (and N_c times
+// the neighbour reads from LDS).  With SS for launches that would leave most of the chip idle (8^3 x 16, N_v = 4: 58 us
+// in FP64, 74 with SS alone; FP32 44 us, 100 in the direct kernel) and rows too short for other forms; without SS in FP64
+// where it fills its wavefronts better (10 x 8 x 9 x 12, N_v = 4: 57 us, 92 with SS).
 //
 // KPS: entries of a window slot that a lane moves at most (1 from about 10 right-hand sides on, N_c = 3).  With a slot
 // limited to one entry per lane fewer right-hand sides took the direct kernel (N_v = 4 at 22 x 18 x 14 x 30, FP32: 1.04 ms
 // against 0.51).
-template <int NC, int RB, bool DAG, class P, int NVC, bool SEG, bool SS, int KPS, bool PF>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SS && (PF || NC == 4) ? 2 : 3))) void brillouin_rows_kernel(const typename P::G* __restrict__ W,
+template <int NC, int RB, bool DAG, class P, int NVC, bool SEG, bool SS, bool CS, int KPS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) || NC == 4 ? 2 : 3))) void brillouin_rows_kernel(const typename P::G* __restrict__ W,
                                                              const typename P::S* __restrict__ in,
                                                              typename P::S* __restrict__ out, typename P::R diag,
                                                              Geom g, int nv, RowTile rt,
@@ -252,7 +254,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SS && (PF |
     using G = typename P::G;
     static_assert(RB == 1, "the row form takes one RHS per thread");
     constexpr int NS = SS ? 2 : 4;       // spins per thread
-    constexpr int NA = SS && PF ? 1 : NC;  // colour rows per thread
+    constexpr int NA = CS ? 1 : NC;      // colour rows per thread
+    constexpr bool PF = !SS || CS;       // the next row copy is in flight during the arithmetic
     constexpr int SHARE = RowUnits<NC, RB, P>::PER * NS * NA, PER = (SHARE + 4 * NC - 1) / (4 * NC);
     constexpr bool EXACT = SHARE % (4 * NC) == 0;  // otherwise lanes past the row copy's units store nothing
     constexpr bool BLOCKPAD = SS && sizeof(typename P::S) == 16;
@@ -272,9 +275,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SS && (PF |
     const uint32_t tt = active ? tid : tid - rt.threads;  // padding threads shadow a real one
     const uint32_t j = fast_div(tt, rt.magic_nrg);      // site within the segment
     const int rg = static_cast<int>(tt - j * rt.nrg);  // SS: (colour *) chirality * nv + rhs
-    const int ca = NA == NC ? 0 : rg / (2 * nv);       // the thread's first colour row
-    const int hs = SS && rg - ca * 2 * nv >= nv ? 1 : 0;  // SS: its chirality
-    const int col0 = rg - (2 * ca + hs) * nv;          // its right-hand side
+    constexpr int NH = SS ? 2 : 1;
+    const int ca = CS ? rg / (NH * nv) : 0;                // the thread's first colour row
+    const int hs = SS && rg - ca * NH * nv >= nv ? 1 : 0;  // SS: its chirality
+    const int col0 = rg - (NH * ca + hs) * nv;             // its right-hand side
     const int x = x0 + static_cast<int>(j);
     int cy, cz, ct;
     {
@@ -326,8 +330,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SS && (PF |
     uint32_t slot[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) slot[k] = SS ? 0u : slot_of(k, tt);
-    // halo units h = tt and tt + threads (< 2 units) copy the sites x0 - 1 (copy site 0) and x0 + S
-    // (copy site S + 1)
+    // halo units h = tt and tt + threads (< 2 units) copy the sites x0 - 1 (copy site 0) and x0 + S (copy site S + 1)
     bool halo[2];
     uint32_t hslot[2];
     uint32_t hsrc[2];  // unit index relative to the start of the copied row
@@ -335,10 +338,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SS && (PF |
     for (int q = 0; q < 2; ++q) {
         const uint32_t h = tt + q * static_cast<uint32_t>(rt.threads);
         halo[q] = SEG && h < 2u * rt.units;
-        const uint32_t hs = h < static_cast<uint32_t>(rt.units) ? 0u : 1u;
-        const uint32_t hcu = h - hs * rt.units;
-        hslot[q] = (hs ? rt.S + 1 : 0) * SU + (BLOCKPAD ? pad_slot(hcu) : hcu);
-        hsrc[q] = static_cast<uint32_t>(hs ? wrap(x0 + rt.S, g.nx) : wrap(x0 - 1, g.nx)) * rt.units + hcu;
+        const uint32_t end = h < static_cast<uint32_t>(rt.units) ? 0u : 1u;
+        const uint32_t hcu = h - end * rt.units;
+        hslot[q] = (end ? rt.S + 1 : 0) * SU + (BLOCKPAD ? pad_slot(hcu) : hcu);
+        hsrc[q] = static_cast<uint32_t>(end ? wrap(x0 + rt.S, g.nx) : wrap(x0 - 1, g.nx)) * rt.units + hcu;
     }
     auto row_start = [&](int rc) __attribute__((always_inline)) {
         const int dy = rc % 3 - 1, dz = (rc / 3) % 3 - 1, dt = rc / 9 - 1;
@@ -651,35 +654,48 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     const size_t block_bytes = static_cast<size_t>(NC) * 4 * a.nv * sizeof(S);
     if (block_bytes % 16 != 0 || !tile_aligned(a)) return false;
     const int units = static_cast<int>(block_bytes / 16);
-    // FP64: two threads per (site, RHS), one per chirality; the other precisions only together with the colour split
     constexpr bool FP64 = sizeof(R) == 8;
     constexpr int kMaxKPS = 3;
-    int nrg = FP64 ? 2 * a.nv : a.nv;  // threads per site
     const int64_t rows = a.g.vol / a.g.nx;
+    // The forms of the kernel: threads per (site, RHS), and the cost of a wavefront in units of one with a thread per
+    // (site, RHS): the share of the work in a lane, times what the form adds to it (measured on lattices of 1890 to
+    // 40040 sites).  FP64: a thread per chirality, or per colour row, whichever fills its wavefronts better, or both; the
+    // other precisions: one thread, or both.
+    struct Form {
+        bool ss, cs;
+        double cost;
+    };
+    const Form kForms[3] = {{FP64, false, FP64 ? 0.5 : 1.0}, {true, true, 0.25}, {false, true, 1.0 / 3}};
+    auto threads_of = [&](const Form& f) { return a.nv * (f.ss ? 2 : 1) * (f.cs ? NC : 1); };
+    auto kps_of = [&](const Form& f, int d) {  // window entries per lane and slot
+        const int th = d * threads_of(f);
+        return ((d == a.g.nx ? d : d + 2) * NC * NC + th - 1) / th;
+    };
+    auto lds_of = [&](const Form& f, int d) {
+        const size_t sc = d + (d != a.g.nx ? 2 : 0);  // sites per copy
+        const size_t su = FP64 && f.ss ? 2 * NC * (2 * a.nv + ss_pad(a.nv)) : units + row_pad(units, a.nv * sizeof(S) / 4);
+        return sc * su * 16 + sc * 3 * NC * NC * sizeof(typename P::G);
+    };
     // Sites per work-group: the whole row or a segment of it (the last one is moved back to end with the row, so it may
     // take some sites again, with the same values), whichever costs a row least: its wavefronts, weighted by the share
     // of the three waves per SIMD that such work-groups fill (measured: four work-groups of 3 wavefronts or three of 4
-    // share a CU, but only one of 5 or 6), plus the copied sites.  At least 64 threads (32 with the colour split), enough of them for the halo (two
-    // units each) and the link window, and 64 KiB of LDS.  FP64, N_v = 12: rows of 16 sites in two segments 1.54 ms, whole
-    // 2.25 (16^3 x 32), rows of 22 in three of 8 2.22 ms, two of 11 4.35; FP32: rows of 22 in two of 11 1.29 ms, two of 16 1.41.
-    auto kps = [&](int d) {  // window entries per lane and slot
-        return ((d == a.g.nx ? d : d + 2) * NC * NC + d * nrg - 1) / (d * nrg);
-    };
-    auto lds_of = [&](int d) {
-        const size_t sc = d + (d != a.g.nx ? 2 : 0);  // sites per copy
-        const size_t su = FP64 ? 2 * NC * (2 * a.nv + ss_pad(a.nv)) : units + row_pad(units, a.nv * sizeof(S) / 4);
-        return sc * su * 16 + sc * 3 * NC * NC * sizeof(typename P::G);
-    };
-    bool split = false;
-    auto choose = [&]() {
+    // share a CU, but only one of 5 or 6), plus the copied sites.  At least 32 threads (the padding lanes of a wavefront
+    // shadow real ones), enough of them for the halo and the link window, and 64 KiB of LDS.  FP64, N_v = 12: rows of 16
+    // sites in two segments 1.54 ms, whole 2.25 (16^3 x 32), rows of 22 in three of 8 2.22 ms, two of 11 4.35; FP32:
+    // rows of 22 in two of 11 1.29 ms, two of 16 1.41.
+    auto waves = [&](const Form& f, int d) { return (d * threads_of(f) + 63) / 64; };
+    auto choose = [&](const Form& f, double& best) {
+        const int nrg = threads_of(f);
         int seg = 0;
-        double best = 0.0;
         for (int d = a.g.nx; d >= 1; --d) {
             const int64_t th = static_cast<int64_t>(d) * nrg;
-            if (th > 512 || th < (split ? 32 : 64) || (d != a.g.nx && units > th) || kps(d) > kMaxKPS || lds_of(d) > 64 * 1024) continue;
-            const int w = static_cast<int>((th + 63) / 64), n = (a.g.nx + d - 1) / d;
+            if (th > 512 || th < 32 || (d != a.g.nx && units > th) || kps_of(f, d) > kMaxKPS ||
+                lds_of(f, d) > 64 * 1024)
+                continue;
+            const int w = waves(f, d), n = (a.g.nx + d - 1) / d;
             const double fill = (w <= 4 ? 12 / w * w : w) / 12.0;
-            const double cost = n * (64 * w / fill + 0.4 * (d + (d == a.g.nx ? 0 : 2)) * nrg);
+            const double more = kps_of(f, d) > 1 && !f.cs ? 1.15 : 1.0;  // registers of a wider window
+            const double cost = f.cost * n * (64 * w * more / fill + 0.4 * (d + (d == a.g.nx ? 0 : 2)) * nrg);
             if (seg == 0 || cost < best) {
                 best = cost;
                 seg = d;
@@ -687,24 +703,31 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
         }
         return seg;
     };
-    int seg = choose();
-    // A thread per colour row and chirality where the launch leaves every SIMD (256 CUs of four) at one wave or none, or
-    // where no segment has enough threads otherwise (FP32, 8^3 x 16: N_v = 4, one wave, 44 against 100 us, N_v = 12, two,
-    // 138 against 77; N_v = 2, direct, 37 against 109)
-    const int base = nrg;
-    if (!a.clover &&
-        (seg == 0 || rows * ((a.g.nx + seg - 1) / seg) * ((seg * nrg + 63) / 64) <= 4 * 256)) {
-        nrg = 2 * NC * a.nv;
-        split = true;
-        if (const int s = choose()) {
-            seg = s;
-        } else {
-            nrg = base;
-            split = false;
+    // A thread per colour row and chirality where such work-groups all run at once (256 CUs of three waves per SIMD): the
+    // longest chain counts there (FP32, 8^3 x 16: N_v = 4 44 against 100 us direct, N_v = 2 37 against 109).
+    double best = 0.0, other = 0.0;
+    int which = 0, seg = choose(kForms[0], best);
+    if (!a.clover) {  // the colour splits carry no clover term
+        for (int k = 1; k < (FP64 ? 3 : 2); ++k) {
+            const int s = choose(kForms[k], other);
+            if (s == 0) continue;
+            const bool resident =
+                k == 1 && rows * ((a.g.nx + s - 1) / s) * waves(kForms[k], s) <= 12 * 256;
+            if (seg == 0 || resident || other <= best * 1.0001) {
+                best = resident ? -1.0 : other;
+                which = k;
+                seg = s;
+            }
         }
     }
-    if (seg == 0) return false;
-    const size_t lds = lds_of(seg);
+    // FP64 where a segment leaves much of a CU empty: the direct kernel costs about 2.1 of these units per (site, RHS) on
+    // a filled chip (N_v = 24 at 13 x 14 x 11 x 20: 1.25 ms, rows 1.62), more where the work-groups all run at once
+    // (6 x 5 x 7 x 9: 108 us, rows 87)
+    const double direct = rows * ((a.g.nx + seg - 1) / std::max(seg, 1)) > 2 * 256 ? 2.1 : 2.2;
+    if (seg == 0 || (FP64 && best > direct * a.g.nx * a.nv)) return false;
+    const Form form = kForms[which];
+    const int nrg = threads_of(form), kps = kps_of(form, seg);
+    const size_t lds = lds_of(form, seg);
     const bool segmented = seg != a.g.nx;
     if (!ensure_spin_table()) return false;  // the direct kernel needs no table
     RowTile rt{};
@@ -718,7 +741,7 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     rt.ntiles = rows * rt.nseg;
     rt.magic_nrg = div_magic(nrg);
     rt.magic_nx = div_magic(a.g.nx);
-    rt.magic_units = div_magic(FP64 ? 2 * a.nv : units);  // the padded blocks of a row copy
+    rt.magic_units = div_magic(FP64 && form.ss ? 2 * a.nv : units);  // the padded blocks of a row copy
     rt.magic_row_units = div_magic(rt.row_units);
     if (!row_order(4, a.g, rt)) return false;
     const int block = (rt.threads + 63) / 64 * 64;
@@ -734,33 +757,43 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     };
     auto pick = [&](auto seg_c) {
         constexpr bool SG = decltype(seg_c)::value;
-        auto with = [&](auto nvc, auto kps_c, auto ss_c, auto pf_c) {
+        auto with = [&](auto nvc, auto ss_c, auto cs_c, auto kps_c) {
             constexpr int NVC = decltype(nvc)::value, KPS = decltype(kps_c)::value;
-            constexpr bool SS = decltype(ss_c)::value, PF = decltype(pf_c)::value;
+            constexpr bool SS = decltype(ss_c)::value, CS = decltype(cs_c)::value;
             if (a.dagger)
-                go(brillouin_rows_kernel<NC, RB, true, P, NVC, SG, SS, KPS, PF>);
+                go(brillouin_rows_kernel<NC, RB, true, P, NVC, SG, SS, CS, KPS>);
             else
-                go(brillouin_rows_kernel<NC, RB, false, P, NVC, SG, SS, KPS, PF>);
+                go(brillouin_rows_kernel<NC, RB, false, P, NVC, SG, SS, CS, KPS>);
         };
         const std::integral_constant<int, 0> any;
         const std::integral_constant<int, 1> one;
         const std::integral_constant<int, kMaxKPS> most;
         const std::true_type yes;
+        const std::false_type no;
         const std::bool_constant<FP64> ss;
-        const std::bool_constant<!FP64> pf;
         constexpr int K12 = NC >= 4 && !FP64 ? 2 : 1;
-        if (split) {
-            if (kps(seg) == 1)
-                with(any, one, yes, yes);
+        if (which == 1) {
+            if (kps == 1)
+                with(any, yes, yes, one);
             else
-                with(any, most, yes, yes);
-        } else if (a.nv == 12 && kps(seg) <= K12) {
-            with(std::integral_constant<int, 12>{}, std::integral_constant<int, K12>{}, ss, pf);
-        } else if (kps(seg) == 1) {
-            with(any, one, ss, pf);
-        } else {
-            with(any, most, ss, pf);
+                with(any, yes, yes, most);
+            return;
         }
+        if constexpr (FP64) {
+            if (which == 2) {
+                if (kps == 1)
+                    with(any, no, yes, one);
+                else
+                    with(any, no, yes, most);
+                return;
+            }
+        }
+        if (a.nv == 12 && kps <= K12)
+            with(std::integral_constant<int, 12>{}, ss, no, std::integral_constant<int, K12>{});
+        else if (kps == 1)
+            with(any, ss, no, one);
+        else
+            with(any, ss, no, most);
     };
     if (segmented)
         pick(std::true_type{});

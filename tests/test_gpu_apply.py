@@ -340,11 +340,12 @@ STAGGERED_ROW_CASES = [
 
 # (dims, nc, nv): a thread per chirality and colour row (small launches), whole rows, segments with a halo whose last one
 # overlaps, and fewer than 64 threads; then launches large enough for the other forms: several window entries per lane,
-# FP64's chirality threads on whole rows and on overlapping segments
+# FP64's chirality threads and colour rows on whole rows and on overlapping segments
 BRILLOUIN_THREAD_CASES = [
     ((8, 2, 3, 2), 3, 4), ((22, 2, 2, 3), 3, 12), ((8, 2, 2, 2), 3, 1), ((5, 3, 2, 2), 2, 13), ((6, 2, 3, 2), 4, 12),
     ((16, 2, 2, 2), 1, 2), ((7, 2, 2, 3), 4, 5), ((4, 2, 2, 2), 3, 3),
     ((16, 9, 12, 10), 3, 4), ((22, 5, 5, 5), 3, 12), ((11, 9, 8, 9), 3, 7), ((16, 8, 8, 9), 2, 12),
+    ((13, 9, 8, 8), 3, 12),
 ]
 
 
