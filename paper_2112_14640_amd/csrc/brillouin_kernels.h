@@ -230,7 +230,8 @@ __host__ __device__ inline uint32_t ss_pad(int nv) {
 // 2 h + 1).  The link product and the -lambda/2 part stay inside a chirality, and the gamma parts of a thread's c go
 // to the other one, so a thread keeps two sums of its size and the partners' are added at the end: the same
 // arithmetic and neighbour reads in twice the wavefronts, with half the sums and row copy registers each.  At one
-// thread per (site, RHS), two waves per SIMD and a work-group of three, the vector unit was busy a third of the time: 1.95 ms at 16^3 x 32 (N_c = 3, N_v = 12), now 1.51, the vector unit 57 % and LDS 55 % busy.
+// thread per (site, RHS), two waves per SIMD and a work-group of three, the vector unit was busy a third of the time:
+// 1.95 ms at 16^3 x 32 (N_c = 3, N_v = 12), now 1.51, the vector unit 57 % and LDS 55 % busy.
 //
 // At three waves per SIMD SS alone has no registers for a row copy in flight during the arithmetic (spilling, 16^3 x 32
 // took 4 ms); the other work-groups of the CU cover the copies instead.

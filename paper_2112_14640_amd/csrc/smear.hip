@@ -26,7 +26,8 @@ struct CM {
 
 // The kernels of a smearing step give a link N_c threads: thread i owns row i of every matrix, so that a product
 // row x matrix needs no exchange and only the right factor is held whole.  Rows meet in LDS where a whole matrix or
-// an adjoint's row is needed.  A work-group takes kStoutLinks links.
+// an adjoint's row is needed.  A work-group takes kStoutLinks links; each XCD takes a contiguous range of them, whose
+// neighbours its L2 then holds (a gather 38 against 39.7 us, a step's first kernel 26.1 against 27.0, at 8^3 x 16).
 constexpr int kStoutLinks = 64;
 
 template <int N>
@@ -141,7 +142,7 @@ __device__ __forceinline__ LinkRow link_row(const Geom& g) {
     LinkRow l;
     l.slot = static_cast<int>(threadIdx.x) / NC;
     l.i = static_cast<int>(threadIdx.x) - l.slot * NC;
-    int64_t link = static_cast<int64_t>(blockIdx.x) * kStoutLinks + l.slot;
+    int64_t link = logical_block() * kStoutLinks + l.slot;
     l.active = link < 4 * g.vol;
     if (!l.active) link = 4 * g.vol - 1;
     l.site = link >> 2;
@@ -649,10 +650,10 @@ int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out,
     auto B = static_cast<const double2*>(b);
     auto O = static_cast<double2*>(out);
     if (which == 0) {
-        hipLaunchKernelGGL((stout_kernel<NC>), dim3(static_cast<unsigned>((4 * g.vol + kStoutLinks - 1) / kStoutLinks)),
+        hipLaunchKernelGGL((stout_kernel<NC>), dim3(static_cast<unsigned>(grid_blocks_x8(4 * g.vol, kStoutLinks))),
                            dim3(kStoutLinks * NC), 0, st, A, O, rho, g);
     } else if (which == 1) {
-        const dim3 grid(static_cast<unsigned>((4 * g.vol + kStoutLinks - 1) / kStoutLinks)), block(kStoutLinks * NC);
+        const dim3 grid(static_cast<unsigned>(grid_blocks_x8(4 * g.vol, kStoutLinks))), block(kStoutLinks * NC);
         auto w = static_cast<double2*>(ws);
         if (w) {
             hipLaunchKernelGGL((stout_backward_kernel<NC, false>), grid, block, 0, st, A, B, O, w, rho, g);
