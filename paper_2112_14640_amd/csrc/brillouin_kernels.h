@@ -586,7 +586,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) 
     }
     __syncthreads();
     S* o = const_cast<S*>(at(static_cast<int>(j) + OFF));
-    if constexpr (SS) {  // the partner's part of this chirality arrives through the thread's own place in the row copy
+    // SS: the partner's part of this chirality arrives through the row copy, which is free by now, in the precision of the
+    // sums: in place where that is the storage precision, else (BF16) one spin after the other, whose sums take as many
+    // bytes as the four spins' elements (8^3 x 16, N_v = 4: 46 us either way)
+    if constexpr (SS && sizeof(S) == sizeof(cx<R>)) {
         S* po = o + (hs ? -static_cast<int>(HB) : static_cast<int>(HB));
         if (active)
 #pragma unroll
@@ -594,6 +597,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) 
 #pragma unroll
                 for (int s = 0; s < NS; ++s) io<R, S>::st(po + el(ca + a, s), oth[a][s]);
         __syncthreads();
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) acc[0][a][s] = cadd(acc[0][a][s], io<R, S>::ld(o + el(ca + a, s)));
+    } else if constexpr (SS) {
+        static_assert(2 * sizeof(S) >= sizeof(cx<R>), "a spin's sums fit the row copy");
+        cx<R>* const ex = reinterpret_cast<cx<R>*>(rtile);  // [colour row of the thread][thread]
+        const uint32_t partner = hs ? tt - nv : tt + nv;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (active)  // a padding thread has no sums
+#pragma unroll
+                for (int a = 0; a < NA; ++a) ex[a * rt.threads + tt] = oth[a][s];
+            __syncthreads();
+#pragma unroll
+            for (int a = 0; a < NA; ++a) acc[0][a][s] = cadd(acc[0][a][s], ex[a * rt.threads + partner]);
+            __syncthreads();
+        }
     }
     if (active) {
 #pragma unroll
@@ -601,11 +622,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) 
 #pragma unroll
             for (int a = 0; a < NA; ++a)
 #pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    cx<R> v = acc[k][a][s];
-                    if constexpr (SS) v = cadd(v, io<R, S>::ld(o + el(ca + a, s)));
-                    io<R, S>::st(o + el(ca + a, s) + k, v);
-                }
+                for (int s = 0; s < NS; ++s) io<R, S>::st(o + el(ca + a, s) + k, acc[k][a][s]);
     }
     __syncthreads();
     u32x4* dst = reinterpret_cast<u32x4*>(out) + (own_start + x0) * rt.units;

@@ -359,6 +359,19 @@ def test_brillouin_thread_forms(case, prec):
     parity(v, ORACLE[("brillouin", dagger)](g_in, u_in, 0.05, True), TOL[prec], (prec, dims, nc, nv))
 
 
+@pytest.mark.parametrize("dims,nc,nv", BRILLOUIN_THREAD_CASES[:8] + [((4, 2, 2, 3), 1, 4), ((6, 2, 2, 2), 2, 2)])
+def test_brillouin_bf16_rounds_once(dims, nc, nv):
+    """BF16 vectors are summed in FP32 and rounded when they are stored, whatever form a launch takes: each real number
+    is within half a unit of its own last place (2^-8 of it) of the exact value, and FP32's error of the largest."""
+    gauge, u = _inputs("brillouin", dims, nc, nv, seed=620 + nv)
+    for dagger in (False, True):
+        v, g_in, u_in = _run("brillouin", "bf16", gauge, u, 0.05, True, dagger)
+        ref = ORACLE[("brillouin", dagger)](g_in, u_in, 0.05, True)
+        fp32 = TOL["fp32"] * np.max(np.abs(ref))
+        for got, want in ((v.real, ref.real), (v.imag, ref.imag)):
+            assert np.max(np.abs(got - want) - 2.0 ** -8 * np.abs(want)) < fp32, (dims, nc, nv, dagger)
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("op,dims,nc,nv", [("wilson", (5, 3, 2, 3), 3, 1), ("wilson", (3, 4, 2, 2), 3, 2),
                                            ("wilson", (7, 3, 3, 2), 2, 1), ("wilson", (3, 2, 5, 2), 4, 2),
