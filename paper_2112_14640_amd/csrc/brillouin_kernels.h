@@ -24,6 +24,7 @@
 #include "clover.h"
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 #include "tile.h"
 
 namespace dirac {
@@ -763,6 +764,7 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     rt.magic_row_units = div_magic(rt.row_units);
     if (!row_order(4, a.g, rt)) return false;
     const int block = (rt.threads + 63) / 64 * 64;
+    if (!fits_launch(rt.ntiles, block)) return false;  // the direct kernel has fewer threads
     const dim3 grid(static_cast<unsigned>(grid_blocks_x8(rt.ntiles, 1)));
     const R diag = static_cast<R>(centre_coefficient(a));
     auto W = static_cast<const typename P::G*>(a.gauge);

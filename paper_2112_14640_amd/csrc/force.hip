@@ -13,6 +13,7 @@
 // (each entry written by exactly one thread).
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace dirac {
 
@@ -129,9 +130,9 @@ template <int NC, int RL>
 __global__ __launch_bounds__(kForceThreads) void brillouin_force_kernel(const double2* __restrict__ psi,
                                                                         const double2* __restrict__ chi,
                                                                         double2* __restrict__ gout, double coeff,
-                                                                        Geom g, int nv, SiteOrder order) {
+                                                                        Geom g, int nv, SiteOrder order, int64_t first) {
     constexpr int LANES = 4 * RL;
-    const int64_t block = logical_block();
+    const int64_t block = first + logical_block();
     const int group = static_cast<int>(block % (40 / kForceDirs));
     const int64_t tile = block / (40 / kForceDirs);
     if (tile * (kForceThreads / LANES) >= g.vol) return;
@@ -262,8 +263,8 @@ template <int NC, int RL>
 __global__ __launch_bounds__(kForceThreads) void wilson_force_kernel(const double2* __restrict__ psi,
                                                                      const double2* __restrict__ chi,
                                                                      double2* __restrict__ gout, double coeff, Geom g,
-                                                                     int nv, SiteOrder order) {
-    const int64_t block = logical_block();
+                                                                     int nv, SiteOrder order, int64_t first) {
+    const int64_t block = first + logical_block();
     if (block * (kForceThreads / (2 * RL)) >= g.vol) return;
     const ForceLane f = force_lane<2 * RL>(block, order, g);
     const Coord c = site_coord(f.site, g);
@@ -278,8 +279,8 @@ template <int NC, int RL>
 __global__ __launch_bounds__(kForceThreads) void staggered_force_kernel(const double2* __restrict__ psi,
                                                                         const double2* __restrict__ chi,
                                                                         double2* __restrict__ gout, double coeff,
-                                                                        Geom g, int nv, SiteOrder order) {
-    const int64_t block = logical_block();
+                                                                        Geom g, int nv, SiteOrder order, int64_t first) {
+    const int64_t block = first + logical_block();
     if (block * (kForceThreads / RL) >= g.vol) return;
     const ForceLane f = force_lane<RL>(block, order, g);
     const Coord c = site_coord(f.site, g);
@@ -353,17 +354,21 @@ void launch_force_rl(dirac_op op, int nv, const Geom& g, const void* psi, const 
     const int sites = kForceThreads / (RL * (op == DIRAC_BRILLOUIN ? 4 : (op == DIRAC_WILSON ? 2 : 1)));  // per block
     const int64_t tiles = (g.vol + sites - 1) / sites;
     const int64_t blocks = op == DIRAC_BRILLOUIN ? tiles * (40 / kForceDirs) : tiles;
-    const dim3 grid(static_cast<unsigned>(grid_blocks_x8(blocks, 1))), block(kForceThreads);
     auto p = static_cast<const double2*>(psi);
     auto c = static_cast<const double2*>(chi);
     auto o = static_cast<double2*>(gout);
     const SiteOrder order = make_site_order(g);
-    if (op == DIRAC_BRILLOUIN)
-        hipLaunchKernelGGL((brillouin_force_kernel<NC, RL>), grid, block, 0, st, p, c, o, coeff, g, nv, order);
-    else if (op == DIRAC_WILSON)
-        hipLaunchKernelGGL((wilson_force_kernel<NC, RL>), grid, block, 0, st, p, c, o, coeff, g, nv, order);
-    else
-        hipLaunchKernelGGL((staggered_force_kernel<NC, RL>), grid, block, 0, st, p, c, o, coeff, g, nv, order);
+    launch_slices(blocks, kForceThreads, [&](int64_t first, unsigned grid) {
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(kForceThreads), 0, st, p, c, o, coeff, g, nv, order, first);
+        };
+        if (op == DIRAC_BRILLOUIN)
+            go(brillouin_force_kernel<NC, RL>);
+        else if (op == DIRAC_WILSON)
+            go(wilson_force_kernel<NC, RL>);
+        else
+            go(staggered_force_kernel<NC, RL>);
+    });
 }
 
 template <int NC>

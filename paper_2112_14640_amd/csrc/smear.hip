@@ -14,6 +14,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace dirac {
 
@@ -138,11 +139,11 @@ struct LinkRow {
     Coord c;
 };
 template <int NC>
-__device__ __forceinline__ LinkRow link_row(const Geom& g) {
+__device__ __forceinline__ LinkRow link_row(const Geom& g, int64_t first) {
     LinkRow l;
     l.slot = static_cast<int>(threadIdx.x) / NC;
     l.i = static_cast<int>(threadIdx.x) - l.slot * NC;
-    int64_t link = logical_block() * kStoutLinks + l.slot;
+    int64_t link = (first + logical_block()) * kStoutLinks + l.slot;
     l.active = link < 4 * g.vol;
     if (!l.active) link = 4 * g.vol - 1;
     l.site = link >> 2;
@@ -262,12 +263,12 @@ __device__ __forceinline__ void exp_rows(CM<NC> A, CM<NC> G, int i, double2* e, 
 // V = exp(i Q) U for every link.  i Q = -(A - Tr A / N) / 2 with A = Omega^+ - Omega.
 template <int NC>
 __global__ __launch_bounds__(kStoutLinks * NC) void stout_kernel(const double2* __restrict__ U, double2* __restrict__ V,
-                                                                 double rho, Geom g) {
+                                                                 double rho, Geom g, int64_t first) {
     constexpr int L = NC * NC;
     __shared__ double2 m0[kStoutLinks][L], m1[kStoutLinks][L];
     __shared__ int squarings;
     if (threadIdx.x == 0) squarings = 0;
-    const LinkRow l = link_row<NC>(g);
+    const LinkRow l = link_row<NC>(g, first);
     double2* const b0 = m0[l.slot];
     double2* const b1 = m1[l.slot];
     const double2* up = U + (l.site * 4 + l.mu) * L;
@@ -291,12 +292,13 @@ template <int NC, bool SCATTER>
 __global__ __launch_bounds__(kStoutLinks * NC) void stout_backward_kernel(const double2* __restrict__ U,
                                                                           const double2* __restrict__ GV,
                                                                           double2* __restrict__ GU,
-                                                                          double2* __restrict__ ws, double rho, Geom g) {
+                                                                          double2* __restrict__ ws, double rho, Geom g,
+                                                                          int64_t first) {
     constexpr int L = NC * NC;
     __shared__ double2 m0[kStoutLinks][L], m1[kStoutLinks][L], m2[kStoutLinks][L];
     __shared__ int squarings;
     if (threadIdx.x == 0) squarings = 0;
-    const LinkRow l = link_row<NC>(g);
+    const LinkRow l = link_row<NC>(g, first);
     double2* const b0 = m0[l.slot];
     double2* const b1 = m1[l.slot];
     double2* const b2 = m2[l.slot];
@@ -378,9 +380,9 @@ __global__ __launch_bounds__(kStoutLinks * NC) void stout_backward_kernel(const 
 template <int NC>
 __global__ __launch_bounds__(kStoutLinks * NC) __attribute__((amdgpu_waves_per_eu(NC <= 3 ? 2 : 1))) void stout_gather_kernel(const double2* __restrict__ U,
                                                                         const double2* __restrict__ ws,
-                                                                        double2* __restrict__ GU, Geom g) {
+                                                                        double2* __restrict__ GU, Geom g, int64_t first) {
     constexpr int L = NC * NC;
-    const LinkRow l = link_row<NC>(g);
+    const LinkRow l = link_row<NC>(g, first);
     if (!l.active) return;
     const int nu = l.mu, i = l.i;
     Row<NC> acc = row_of<NC>(ws + ((g.vol + l.site) * 4 + nu) * L, i);
@@ -500,12 +502,12 @@ __constant__ TransDirs c_trans = make_trans_dirs();
 
 template <int NC>
 __global__ __launch_bounds__(kSplitSites * kSplitGroups * NC) void links_backward_kernel(
-    const double2* __restrict__ V, const double2* __restrict__ GW, double2* __restrict__ GV, Geom g) {
+    const double2* __restrict__ V, const double2* __restrict__ GW, double2* __restrict__ GV, Geom g, int64_t first) {
     constexpr int S = kSplitSites, L = NC * NC, T = S * kSplitGroups * NC;
     __shared__ cx<double> w[S][2][27][L];  // path averages in the three other axes at m and m + mu (13: identity)
     __shared__ int disp[S][2][27];         // their sites' offsets from m (32 bits: V < 2^31)
     __shared__ uint32_t pairs[kSplitGroups * kSplitPairs];
-    const int64_t block = logical_block();
+    const int64_t block = first + logical_block();
     const int mu = static_cast<int>(block & 3);
     const int64_t site0 = (block >> 2) * S;
     if (site0 >= g.vol) return;
@@ -649,22 +651,25 @@ int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out,
     auto A = static_cast<const double2*>(a);
     auto B = static_cast<const double2*>(b);
     auto O = static_cast<double2*>(out);
+    auto slices = [&](int64_t blocks, int threads, auto kern, auto... args) {
+        launch_slices(blocks, threads, [&](int64_t first, unsigned grid) {
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, args..., g, first);
+        });
+    };
+    const int64_t groups = (4 * g.vol + kStoutLinks - 1) / kStoutLinks;
     if (which == 0) {
-        hipLaunchKernelGGL((stout_kernel<NC>), dim3(static_cast<unsigned>(grid_blocks_x8(4 * g.vol, kStoutLinks))),
-                           dim3(kStoutLinks * NC), 0, st, A, O, rho, g);
+        slices(groups, kStoutLinks * NC, stout_kernel<NC>, A, O, rho);
     } else if (which == 1) {
-        const dim3 grid(static_cast<unsigned>(grid_blocks_x8(4 * g.vol, kStoutLinks))), block(kStoutLinks * NC);
         auto w = static_cast<double2*>(ws);
         if (w) {
-            hipLaunchKernelGGL((stout_backward_kernel<NC, false>), grid, block, 0, st, A, B, O, w, rho, g);
-            hipLaunchKernelGGL((stout_gather_kernel<NC>), grid, block, 0, st, A, w, O, g);
+            slices(groups, kStoutLinks * NC, stout_backward_kernel<NC, false>, A, B, O, w, rho);
+            slices(groups, kStoutLinks * NC, stout_gather_kernel<NC>, A, static_cast<const double2*>(w), O);
         } else {
-            hipLaunchKernelGGL((stout_backward_kernel<NC, true>), grid, block, 0, st, A, B, O, w, rho, g);
+            slices(groups, kStoutLinks * NC, stout_backward_kernel<NC, true>, A, B, O, w, rho);
         }
     } else {
-        const int64_t blocks = (g.vol + kSplitSites - 1) / kSplitSites * 4;
-        hipLaunchKernelGGL((links_backward_kernel<NC>), dim3(static_cast<unsigned>(grid_blocks_x8(blocks, 1))),
-                           dim3(kSplitSites * kSplitGroups * NC), 0, st, A, B, O, g);
+        slices((g.vol + kSplitSites - 1) / kSplitSites * 4, kSplitSites * kSplitGroups * NC, links_backward_kernel<NC>,
+               A, B, O);
     }
     return DIRAC_OK;
 }
