@@ -18,6 +18,7 @@
 // the spin-trivial part of the stencil (the rho terms are skipped; the caller passes the diagonal).
 #pragma once
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -676,6 +677,9 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     constexpr bool FP64 = sizeof(R) == 8;
     constexpr int kMaxKPS = 3;
     const int64_t rows = a.g.vol / a.g.nx;
+    // the kernel addresses a row of the vectors and of the links with 32-bit byte offsets
+    constexpr int kLinkBytes = 40 * NC * NC * static_cast<int>(sizeof(typename P::G));
+    if (a.g.nx > static_cast<int64_t>(UINT32_MAX) / std::max(units * 16, kLinkBytes)) return false;
     // The forms of the kernel: threads per (site, RHS), and the cost of a wavefront in units of one with a thread per
     // (site, RHS): the share of the work in a lane, times what the form adds to it (measured on lattices of 1890 to
     // 40040 sites).  FP64: a thread per chirality, or per colour row, whichever fills its wavefronts better, or both; the
@@ -706,9 +710,9 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     auto choose = [&](const Form& f, double& best) {
         const int nrg = threads_of(f);
         int seg = 0;
-        for (int d = a.g.nx; d >= 1; --d) {
-            const int64_t th = static_cast<int64_t>(d) * nrg;
-            if (th > 512 || th < 32 || (d != a.g.nx && units > th) || kps_of(f, d) > kMaxKPS ||
+        for (int d = std::min(a.g.nx, 512 / nrg); d >= 1; --d) {
+            const int th = d * nrg;
+            if (th < 32 || (d != a.g.nx && units > th) || kps_of(f, d) > kMaxKPS ||
                 lds_of(f, d) > 64 * 1024)
                 continue;
             const int w = waves(f, d), n = (a.g.nx + d - 1) / d;
