@@ -19,7 +19,6 @@
 #pragma once
 
 #include <algorithm>
-#include <mutex>
 #include <type_traits>
 
 #include "clover.h"
@@ -35,23 +34,39 @@ namespace {
 __constant__ double c_rho[5] = {0.0, 64.0 / 432.0, 16.0 / 432.0, 4.0 / 432.0, 1.0 / 432.0};
 __constant__ double c_halflam[5] = {-120.0 / 64.0, 4.0 / 64.0, 2.0 / 64.0, 1.0 / 64.0, 0.5 / 64.0};
 
-// Spin-factor scalars per direction, filled once per device from the two tables above:
-// c_spin<R>[dag][flip][dir] = {lambda_k / 2, q_1..q_4} with q_mu = rho_k d_mu (negated for the adjoint)
-// and all five negated when flip = 1 (the fermion sign of a t-wrapping hop).  Wave-uniform, so the
-// row kernel reads them with scalar loads instead of recomputing them in every lane.
-constexpr int kSpinVals = 5;
-__constant__ float c_spin_f[2][2][81][kSpinVals];
-__constant__ double c_spin_d[2][2][81][kSpinVals];
+// Spin-factor scalars per direction: {lambda_k / 2, q_1..q_4} with q_mu = rho_k d_mu (negated for the adjoint).
+// Wave-uniform, so the row kernel reads them with scalar loads instead of recomputing them in every lane.  A constant of
+// the code object, so that a first launch uploads nothing (it may be one that a stream captures).
+template <typename R>
+struct SpinTable {
+    R at[2][81][5];  // [dagger][dir]
+};
+template <typename R>
+constexpr SpinTable<R> make_spin_table() {
+    SpinTable<R> t{};
+    const double rho[5] = {0.0, 64.0 / 432.0, 16.0 / 432.0, 4.0 / 432.0, 1.0 / 432.0};
+    const double halflam[5] = {-120.0 / 64.0, 4.0 / 64.0, 2.0 / 64.0, 1.0 / 64.0, 0.5 / 64.0};
+    for (int dag = 0; dag < 2; ++dag)
+        for (int dir = 0; dir < 81; ++dir) {
+            const int d[4] = {dir % 3 - 1, (dir / 3) % 3 - 1, (dir / 9) % 3 - 1, dir / 27 - 1};
+            const int k = (d[0] != 0) + (d[1] != 0) + (d[2] != 0) + (d[3] != 0);
+            t.at[dag][dir][0] = static_cast<R>(halflam[k]);
+            for (int mu = 0; mu < 4; ++mu) t.at[dag][dir][1 + mu] = static_cast<R>((dag ? -rho[k] : rho[k]) * d[mu]);
+        }
+    return t;
+}
+__constant__ SpinTable<float> c_spin_f = make_spin_table<float>();
+__constant__ SpinTable<double> c_spin_d = make_spin_table<double>();
 
 template <typename R>
-__device__ __forceinline__ const R* spin_table(int dag, int flip, int dir);
+__device__ __forceinline__ const R* spin_table(int dag, int dir);
 template <>
-__device__ __forceinline__ const float* spin_table<float>(int dag, int flip, int dir) {
-    return c_spin_f[dag][flip][dir];
+__device__ __forceinline__ const float* spin_table<float>(int dag, int dir) {
+    return c_spin_f.at[dag][dir];
 }
 template <>
-__device__ __forceinline__ const double* spin_table<double>(int dag, int flip, int dir) {
-    return c_spin_d[dag][flip][dir];
+__device__ __forceinline__ const double* spin_table<double>(int dag, int dir) {
+    return c_spin_d.at[dag][dir];
 }
 
 // ---------------------------------------------------------------------------
@@ -553,8 +568,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) 
                     }
                 }
             }
-            const R* sm = spin_table<R>(DAG ? 1 : 0, 0, dir0);
-            const R* sp = spin_table<R>(DAG ? 1 : 0, 0, dir0 + 2);
+            const R* sm = spin_table<R>(DAG ? 1 : 0, dir0);
+            const R* sp = spin_table<R>(DAG ? 1 : 0, dir0 + 2);
             // The three hops of a row share one accumulator c.  With k the number of non-zero components of
             // d_x = +-1 (and k - 1 for d_x = 0), S_pm = -l + R pm q gamma_x with l = lambda_k / 2 and
             // R = sum over y, z, t of rho_k d_mu gamma_mu; the d_x = 0 hop has S_0 = -2 l + 4 R (rho and
@@ -632,35 +647,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) 
     for (uint32_t u = tid; u < total; u += blockDim.x) dst[u] = rtile[pad_slot(u) + OFF * SU];
 }
 
-
-// Fill c_spin_f / c_spin_d on the current device (once per device, thread-safe).  false on failure.
-bool ensure_spin_table() {
-    static std::mutex mu;
-    static bool done[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-    std::lock_guard<std::mutex> lock(mu);
-    if (done[dev]) return true;
-    const double rho[5] = {0.0, 64.0 / 432.0, 16.0 / 432.0, 4.0 / 432.0, 1.0 / 432.0};
-    const double halflam[5] = {-120.0 / 64.0, 4.0 / 64.0, 2.0 / 64.0, 1.0 / 64.0, 0.5 / 64.0};
-    static double td[2][2][81][kSpinVals];
-    static float tf[2][2][81][kSpinVals];
-    for (int dag = 0; dag < 2; ++dag)
-        for (int flip = 0; flip < 2; ++flip)
-            for (int dir = 0; dir < 81; ++dir) {
-                const int d[4] = {dir % 3 - 1, (dir / 3) % 3 - 1, (dir / 9) % 3 - 1, dir / 27 - 1};
-                const int k = (d[0] != 0) + (d[1] != 0) + (d[2] != 0) + (d[3] != 0);
-                const double sg = flip ? -1.0 : 1.0;
-                const double r = sg * (dag ? -rho[k] : rho[k]);
-                td[dag][flip][dir][0] = sg * halflam[k];
-                for (int mu = 0; mu < 4; ++mu) td[dag][flip][dir][1 + mu] = r * d[mu];
-                for (int v = 0; v < kSpinVals; ++v) tf[dag][flip][dir][v] = static_cast<float>(td[dag][flip][dir][v]);
-            }
-    if (hipMemcpyToSymbol(HIP_SYMBOL(c_spin_d), td, sizeof(td)) != hipSuccess) return false;
-    if (hipMemcpyToSymbol(HIP_SYMBOL(c_spin_f), tf, sizeof(tf)) != hipSuccess) return false;
-    done[dev] = true;
-    return true;
-}
 
 // The centre coefficient: m - lambda_0/2 for D_B, m^2/2 - lambda_0/2 for the Laplacian.
 double centre_coefficient(const StencilArgs& a) {
@@ -752,7 +738,6 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     const int nrg = threads_of(form), kps = kps_of(form, seg);
     const size_t lds = lds_of(form, seg);
     const bool segmented = seg != a.g.nx;
-    if (!ensure_spin_table()) return false;  // the direct kernel needs no table
     RowTile rt{};
     rt.R = 1;
     rt.S = seg;
