@@ -104,8 +104,8 @@ int check_hip(hipError_t e, const char* what) {
 //              BF16 stage each direction's links in LDS, FP64 loads them per thread.
 //   Wilson Laplacian: the staggered row kernel on 4 Nv columns, 4 per thread.
 //   Brillouin (and its Laplacian): row tiles (27 row copies per x-row, link windows in LDS), 1 RHS per thread in FP32
-//              and BF16, two threads per RHS (one per chirality) in FP64, and one per colour row and chirality in
-//              launches that leave most of the chip idle or rows too short for 64 threads otherwise.
+//              and BF16, two threads per RHS (one per chirality) in FP64, more in launches that leave most of the chip
+//              idle and on short rows (brillouin_plan.h).
 // Row tiles fall back to direct loads for shapes they cannot take; an rb that does not divide the
 // columns falls back to 1.
 int choose_rb(dirac_op op, dirac_prec prec, int nc, int nv, const Geom& g) {

@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "brillouin_plan.h"
 #include "clover.h"
 #include "common.h"
 #include "kernels.h"
@@ -254,15 +255,16 @@ __host__ __device__ inline uint32_t ss_pad(int nv) {
 // took 4 ms); the other work-groups of the CU cover the copies instead.
 //
 // CS: every colour row has a thread of its own, N_c times the wavefronts with an N_c-th of the work each (and N_c times
-// the neighbour reads from LDS).  With SS for launches that would leave most of the chip idle (8^3 x 16, N_v = 4: 58 us
-// in FP64, 74 with SS alone; FP32 44 us, 100 in the direct kernel) and rows too short for other forms; without SS in FP64
-// where it fills its wavefronts better (10 x 8 x 9 x 12, N_v = 4: 57 us, 92 with SS).
+// the neighbour reads from LDS).  With SS for launches that would leave most of the chip idle (8^3 x 16, N_v = 4: 59 us
+// in FP64, 78 with SS alone; FP32 45 us, 76 with one thread, 99 in the direct kernel) and rows too short for other forms;
+// without SS in FP64 where it fills its wavefronts better (10 x 8 x 9 x 12, N_v = 4: 57 us, 90 with SS, 63 with one
+// thread at two waves per SIMD).  brillouin_plan.h chooses.
 //
 // KPS: entries of a window slot that a lane moves at most (1 from about 10 right-hand sides on, N_c = 3).  With a slot
 // limited to one entry per lane fewer right-hand sides took the direct kernel (N_v = 4 at 22 x 18 x 14 x 30, FP32: 1.04 ms
 // against 0.51).
 template <int NC, int RB, bool DAG, class P, int NVC, bool SEG, bool SS, bool CS, int KPS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) || NC == 4 ? 2 : 3))) void brillouin_rows_kernel(const typename P::G* __restrict__ W,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu((SS && CS) || NC == 4 || (sizeof(typename P::R) == 8 && !SS && !CS && NC == 2) ? 2 : 3))) void brillouin_rows_kernel(const typename P::G* __restrict__ W,
                                                              const typename P::S* __restrict__ in,
                                                              typename P::S* __restrict__ out, typename P::R diag,
                                                              Geom g, int nv, RowTile rt,
@@ -661,81 +663,22 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     if (block_bytes % 16 != 0 || !tile_aligned(a)) return false;
     const int units = static_cast<int>(block_bytes / 16);
     constexpr bool FP64 = sizeof(R) == 8;
-    constexpr int kMaxKPS = 3;
-    const int64_t rows = a.g.vol / a.g.nx;
     // the kernel addresses a row of the vectors and of the links with 32-bit byte offsets
     constexpr int kLinkBytes = 40 * NC * NC * static_cast<int>(sizeof(typename P::G));
     if (a.g.nx > static_cast<int64_t>(UINT32_MAX) / std::max(units * 16, kLinkBytes)) return false;
-    // The forms of the kernel: threads per (site, RHS), and the cost of a wavefront in units of one with a thread per
-    // (site, RHS): the share of the work in a lane, times what the form adds to it (measured on lattices of 1890 to
-    // 40040 sites).  FP64: a thread per chirality, or per colour row, whichever fills its wavefronts better, or both; the
-    // other precisions: one thread, or both.
-    struct Form {
-        bool ss, cs;
-        double cost;
-    };
-    const Form kForms[3] = {{FP64, false, FP64 ? 0.5 : 1.0}, {true, true, 0.25}, {false, true, 1.0 / 3}};
-    auto threads_of = [&](const Form& f) { return a.nv * (f.ss ? 2 : 1) * (f.cs ? NC : 1); };
-    auto kps_of = [&](const Form& f, int d) {  // window entries per lane and slot
-        const int th = d * threads_of(f);
-        return ((d == a.g.nx ? d : d + 2) * NC * NC + th - 1) / th;
-    };
-    auto lds_of = [&](const Form& f, int d) {
+    const int64_t rows = a.g.vol / a.g.nx;
+    auto lds_of = [&](const RowForm& f, int d) {
         const size_t sc = d + (d != a.g.nx ? 2 : 0);  // sites per copy
-        const size_t su = FP64 && f.ss ? 2 * NC * (2 * a.nv + ss_pad(a.nv)) : units + row_pad(units, a.nv * sizeof(S) / 4);
+        const size_t su = FP64 && f.chirality ? 2 * NC * (2 * a.nv + ss_pad(a.nv))
+                                              : units + row_pad(units, a.nv * sizeof(S) / 4);
         return sc * su * 16 + sc * 3 * NC * NC * sizeof(typename P::G);
     };
-    // Sites per work-group: the whole row or a segment of it (the last one is moved back to end with the row, so it may
-    // take some sites again, with the same values), whichever costs a row least: its wavefronts, weighted by the share
-    // of the three waves per SIMD that such work-groups fill (measured: four work-groups of 3 wavefronts or three of 4
-    // share a CU, but only one of 5 or 6), plus the copied sites.  At least 32 threads (the padding lanes of a wavefront
-    // shadow real ones), enough of them for the halo and the link window, and 64 KiB of LDS.  FP64, N_v = 12: rows of 16
-    // sites in two segments 1.54 ms, whole 2.25 (16^3 x 32), rows of 22 in three of 8 2.22 ms, two of 11 4.35; FP32:
-    // rows of 22 in two of 11 1.29 ms, two of 16 1.41.
-    auto waves = [&](const Form& f, int d) { return (d * threads_of(f) + 63) / 64; };
-    auto choose = [&](const Form& f, double& best) {
-        const int nrg = threads_of(f);
-        int seg = 0;
-        for (int d = std::min(a.g.nx, 512 / nrg); d >= 1; --d) {
-            const int th = d * nrg;
-            if (th < 32 || (d != a.g.nx && units > th) || kps_of(f, d) > kMaxKPS ||
-                lds_of(f, d) > 64 * 1024)
-                continue;
-            const int w = waves(f, d), n = (a.g.nx + d - 1) / d;
-            const double fill = (w <= 4 ? 12 / w * w : w) / 12.0;
-            const double more = kps_of(f, d) > 1 && !f.cs ? 1.15 : 1.0;  // registers of a wider window
-            const double cost = f.cost * n * (64 * w * more / fill + 0.4 * (d + (d == a.g.nx ? 0 : 2)) * nrg);
-            if (seg == 0 || cost < best) {
-                best = cost;
-                seg = d;
-            }
-        }
-        return seg;
-    };
-    // A thread per colour row and chirality where such work-groups all run at once (256 CUs of three waves per SIMD): the
-    // longest chain counts there (FP32, 8^3 x 16: N_v = 4 44 against 100 us direct, N_v = 2 37 against 109).
-    double best = 0.0, other = 0.0;
-    int which = 0, seg = choose(kForms[0], best);
-    if (!a.clover) {  // the colour splits carry no clover term
-        for (int k = 1; k < (FP64 ? 3 : 2); ++k) {
-            const int s = choose(kForms[k], other);
-            if (s == 0) continue;
-            const bool resident =
-                k == 1 && rows * ((a.g.nx + s - 1) / s) * waves(kForms[k], s) <= 12 * 256;
-            if (seg == 0 || resident || other <= best * 1.0001) {
-                best = resident ? -1.0 : other;
-                which = k;
-                seg = s;
-            }
-        }
-    }
-    // FP64 where a segment leaves much of a CU empty: the direct kernel costs about 2.1 of these units per (site, RHS) on
-    // a filled chip (N_v = 24 at 13 x 14 x 11 x 20: 1.25 ms, rows 1.62), more where the work-groups all run at once
-    // (6 x 5 x 7 x 9: 108 us, rows 87)
-    const double direct = rows * ((a.g.nx + seg - 1) / std::max(seg, 1)) > 2 * 256 ? 2.1 : 2.2;
-    if (seg == 0 || (FP64 && best > direct * a.g.nx * a.nv)) return false;
-    const Form form = kForms[which];
-    const int nrg = threads_of(form), kps = kps_of(form, seg);
+    const RowPlan plan =
+        plan_rows({NC, a.nv, static_cast<int>(sizeof(S)), a.g.nx, rows, a.clover != nullptr}, lds_of);
+    if (plan.form < 0) return false;
+    const RowForm form = row_form(FP64, plan.form);
+    const int seg = plan.seg, kps = plan.entries;
+    const int nrg = a.nv * (form.chirality ? 2 : 1) * (form.colour ? NC : 1);
     const size_t lds = lds_of(form, seg);
     const bool segmented = seg != a.g.nx;
     RowTile rt{};
@@ -749,7 +692,7 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     rt.ntiles = rows * rt.nseg;
     rt.magic_nrg = div_magic(nrg);
     rt.magic_nx = div_magic(a.g.nx);
-    rt.magic_units = div_magic(FP64 && form.ss ? 2 * a.nv : units);  // the padded blocks of a row copy
+    rt.magic_units = div_magic(FP64 && form.chirality ? 2 * a.nv : units);  // the padded blocks of a row copy
     rt.magic_row_units = div_magic(rt.row_units);
     if (!row_order(4, a.g, rt)) return false;
     const int block = (rt.threads + 63) / 64 * 64;
@@ -776,12 +719,12 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
         };
         const std::integral_constant<int, 0> any;
         const std::integral_constant<int, 1> one;
-        const std::integral_constant<int, kMaxKPS> most;
+        const std::integral_constant<int, kMaxWindowEntries> most;
         const std::true_type yes;
         const std::false_type no;
         const std::bool_constant<FP64> ss;
         constexpr int K12 = NC >= 4 && !FP64 ? 2 : 1;
-        if (which == 1) {
+        if (plan.form == 1) {
             if (kps == 1)
                 with(any, yes, yes, one);
             else
@@ -789,12 +732,21 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
             return;
         }
         if constexpr (FP64) {
-            if (which == 2) {
+            if (plan.form == 2) {
                 if (kps == 1)
                     with(any, no, yes, one);
                 else
                     with(any, no, yes, most);
                 return;
+            }
+            if constexpr (NC <= 2) {
+                if (plan.form == 3) {
+                    if (kps == 1)
+                        with(any, no, no, one);
+                    else
+                        with(any, no, no, most);
+                    return;
+                }
             }
         }
         if (a.nv == 12 && kps <= K12)

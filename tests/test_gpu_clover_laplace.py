@@ -101,6 +101,31 @@ def test_clover_apply_small(case, op, prec, variant):
         dirac.set_launch_shape(op, prec, 0, 0)
 
 
+# (dims, nc, nv): the forms of the Brillouin row kernel that N_c = 1, 2 and 4 take, on whole rows and on segments with and
+# without overlap; those with a clover field are fewer, so each shape runs with and without one
+FORM_CASES = [
+    ((4, 2, 2, 2), 1, 8), ((13, 2, 2, 2), 1, 5), ((8, 2, 2, 2), 1, 8), ((5, 2, 2, 2), 1, 16), ((13, 5, 2, 9), 1, 16),
+    ((5, 5, 7, 8), 2, 12), ((13, 2, 8, 9), 2, 12), ((16, 5, 4, 5), 2, 16), ((6, 5, 7, 5), 2, 24), ((9, 2, 2, 2), 2, 2),
+    ((5, 5, 2, 9), 4, 24), ((9, 3, 2, 9), 4, 24), ((12, 2, 2, 2), 4, 1), ((8, 8, 3, 8), 4, 4),
+]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("dims,nc,nv", FORM_CASES)
+def test_brillouin_forms_by_colours(dims, nc, nv, prec):
+    rng = np.random.default_rng(330 + nc + nv)
+    U = si.gauge_field(rng, dims, nc, "haar")
+    Ud, Uo = _links(U, prec)
+    W = brillouin_links(Uo)
+    gauge = to_dev(W) if prec == "fp64" else to_dev(W, torch.complex64)
+    ud, u_in = _vec(si.wilson_vector(rng, dims, nc, nv), prec)
+    ref = brillouin_apply(W, u_in, 0.08, True)
+    parity(_host(dirac.apply("brillouin", gauge, ud, 0.08), prec), ref, TOL[prec], (dims, nc, nv, prec))
+    ref = ref + clover_apply(field_strength(Uo), u_in, 1.0)
+    v = _host(dirac.apply("brillouin", gauge, ud, 0.08, clover=dirac.clover_field(Ud, 1.0)), prec)
+    parity(v, ref, TOL[prec], (dims, nc, nv, prec, "clover"))
+
+
 @pytest.mark.parametrize("prec", ["fp32", "bf16"])
 @pytest.mark.parametrize("op", ["wilson", "brillouin"])
 def test_clover_apply_16x32_sampled(op, prec):
