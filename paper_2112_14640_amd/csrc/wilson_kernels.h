@@ -236,7 +236,7 @@ struct RowLinks {
     static constexpr int PER = NVC > 0 ? (NC * NC + NVC / RB - 1) / (NVC / RB) : 3;
 };
 
-template <int NC, int RB, bool DAG, class P, int NVC, bool LL, bool CLOV>
+template <int NC, int RB, bool DAG, class P, int NVC, bool LL, int CLOV>
 __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* __restrict__ U,
                                                           const typename P::S* __restrict__ in,
                                                           typename P::S* __restrict__ out, typename P::R diag,
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
         load_link<NC, false, P>(lxp, U + (site * 4 + 0) * L);
         load_link<NC, true, P>(lxm, U + ((rowsite + xm) * 4 + 0) * L);
     }
-    if constexpr (CLOV) {
+    if constexpr (CLOV == 2) {
         constexpr uint32_t CU = clover_reals<NC>() * sizeof(R) / 16;  // units per site
         stage(lclov_u, reinterpret_cast<const u32x4*>(clov) + rowsite * CU, static_cast<uint32_t>(rt.S) * CU);
     }
@@ -365,7 +365,8 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
             for (int a = 0; a < NC; ++a)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) acc[k][a][s] = cscale(diag, io<R, S>::ld(mine + (a * 4 + s) * nv + k));
-        if constexpr (CLOV)
+        if constexpr (CLOV == 1) clover_add<NC, RB>(acc, mine, nv, clov + site * clover_reals<NC>());
+        if constexpr (CLOV == 2)
             clover_add<NC, RB>(acc, mine, nv, reinterpret_cast<const R*>(lclov_u) + x * clover_reals<NC>());
     };
     // with a clover field the site's clover block is applied from the own row before the x links are
@@ -486,15 +487,16 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     // the links (and the clover field) staged in LDS after the row tile, where a thread moves at most LPER entries of a
     // neighbour row's links and the device has the room (beyond the row tile's own cap)
     const size_t nlink = static_cast<size_t>(rt.S) * NC * NC * sizeof(typename P::G);
-    const size_t lds_cl = a.clover ? static_cast<size_t>(rt.S) * clover_reals<NC>() * sizeof(typename P::R) : 0;
-    if (a.clover && (reinterpret_cast<uintptr_t>(a.clover) % 16 != 0 || lds + lds_cl > max_lds_per_block())) return false;
-    const size_t lds_ll = lds + 4 * nlink + (nlink + 15) / 16 * 16 + lds_cl;
+    const size_t lds_cl = static_cast<size_t>(rt.S) * clover_reals<NC>() * sizeof(typename P::R);
+    const bool stage_cl = a.clover && reinterpret_cast<uintptr_t>(a.clover) % 16 == 0 && lds + lds_cl <= max_lds_per_block();
+    if (stage_cl) lds += lds_cl;
+    const size_t lds_ll = lds + 4 * nlink + (nlink + 15) / 16 * 16;
     // FP64 takes it at N_v = 12 only: with N_v known at run time the entries in flight spill (24^3 x 48, N_v = 4: 0.69
     // against 0.55 ms with a link per thread)
     constexpr bool kFP64 = sizeof(typename P::R) == 8;
     const bool ll = NC * NC <= RowLinks<NC, RB, 0>::PER * nrg && lds_ll <= max_lds_per_block() &&
                     (!kFP64 || (a.nv == 12 && RB == 1));
-    lds = ll ? lds_ll : lds + lds_cl;
+    if (ll) lds = lds_ll;
     const dim3 grid(static_cast<unsigned>(grid_blocks_x8(rt.ntiles, 1)));
     using R = typename P::R;
     const R diag = static_cast<R>(4.0 + a.mass);
@@ -513,7 +515,7 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     // the clover term is a separate instantiation: its registers would otherwise lower the occupancy
     // of the plain kernel
     auto pick = [&](auto clov_c) {
-        constexpr bool CL = decltype(clov_c)::value;
+        constexpr int CL = decltype(clov_c)::value;
         if (ll) {
             if constexpr (RB == 1) {
                 if (a.nv == 12) {  // the RHS stride as a compile-time constant
@@ -538,10 +540,12 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
         else
             go(wilson_rows_kernel<NC, RB, false, P, 0, false, CL>);
     };
-    if (clov)
-        pick(std::true_type{});
+    if (!clov)
+        pick(std::integral_constant<int, 0>{});
+    else if (!stage_cl)
+        pick(std::integral_constant<int, 1>{});
     else
-        pick(std::false_type{});
+        pick(std::integral_constant<int, 2>{});
     return ok;
 }
 

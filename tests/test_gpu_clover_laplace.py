@@ -101,6 +101,21 @@ def test_clover_apply_small(case, op, prec, variant):
         dirac.set_launch_shape(op, prec, 0, 0)
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("dims,nc,nv", [((16, 2, 2, 3), 3, 12), ((12, 2, 3, 2), 3, 8), ((16, 3, 2, 2), 2, 4),
+                                        ((64, 2, 2, 2), 4, 1)])
+def test_clover_field_off_16_byte_boundaries(dims, nc, nv, prec):
+    """A clover field that is aligned to its own elements only takes the row kernel as well (whose sums are in another
+    order than the direct kernel's): the same bits as an aligned field."""
+    rng = np.random.default_rng(350 + nv)
+    Ud, _ = _links(si.gauge_field(rng, dims, nc, "haar"), prec)
+    ud, _ = _vec(si.wilson_vector(rng, dims, nc, nv), prec)
+    C = dirac.clover_field(Ud, 1.0)
+    shifted = torch.empty(C.numel() + 1, dtype=C.dtype, device=C.device)[1:].view(C.shape).copy_(C)
+    assert C.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 != 0
+    assert torch.equal(dirac.apply("wilson", Ud, ud, 0.1, clover=C), dirac.apply("wilson", Ud, ud, 0.1, clover=shifted))
+
+
 # (dims, nc, nv): the forms of the Brillouin row kernel that N_c = 1, 2 and 4 take, on whole rows and on segments with and
 # without overlap; those with a clover field are fewer, so each shape runs with and without one
 FORM_CASES = [
