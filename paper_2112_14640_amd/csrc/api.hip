@@ -98,8 +98,9 @@ int check_hip(hipError_t e, const char* what) {
 // Default launch shapes, chosen by timing the shapes at 16^3 x 32 and 32^3 x 64, Nc = 3, Nv = 12 on
 // MI355X:
 //   Wilson: row tiles (one x-row per work-group staged in LDS), 1 RHS per thread (2 where a row of
-//           single-RHS threads would exceed 512 threads); with Nv = 12 each direction's links are
-//           staged in LDS beside the row and the RHS stride is a compile-time constant.
+//           single-RHS threads would exceed 512 threads); links and clover records staged in LDS beside the
+//           row where that pays (launch_rows in wilson_kernels.h); with Nv = 12 and staged links the RHS
+//           stride is a compile-time constant.
 //   staggered: row tiles, 2 RHS per thread (4 where 2 would exceed 512 threads per row); FP32 and
 //              BF16 stage each direction's links in LDS, FP64 loads them per thread.
 //   Wilson Laplacian: the staggered row kernel on 4 Nv columns, 4 per thread.

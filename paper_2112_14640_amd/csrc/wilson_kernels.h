@@ -12,6 +12,7 @@
 // antiperiodic in t.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "clover.h"
@@ -219,15 +220,17 @@ __global__ __launch_bounds__(256) void wilson_kernel(const typename P::G* __rest
 // loads of one direction overlap the arithmetic of the previous one.  The output tile leaves
 // through LDS as one contiguous store.
 //
-// With LL the links are staged in LDS beside the row copy: the row's own four links per site, one contiguous block,
-// once at the start (they serve the four forward hops and the -x hop), and per backward hop the one link per site of
-// the neighbour row, an N_c x N_c block of its four.  Taken direction by direction, a 72-byte block per 288-byte site,
-// the own links are 128-byte lines touched four times far apart: 103.6 against 100.9 us at 16^3 x 32 (FP32, N_c = 3,
-// N_v = 12; 531 and 515 MB fetched, bound by the fabric, since a row leaves L2 between its seven uses).
-// Without LL (a thread of a site would have more than LPER entries to move, or no room) every thread loads its own
-// link one direction ahead.  CLOV: the site's clover record is staged as well (contiguous, 16 bytes a lane) instead of
-// being read by every right-hand side's thread (with the links 1.70 against 1.63 ms for BF16 vectors at 32^3 x 64, which
-// the vector instructions bound: 1.46 ms with the BF16 stores converted in hardware).
+// LL: the links are staged in LDS beside the row copy.  LL 2 (FP32, BF16): the row's own four links per site, one
+// contiguous block, once at the start (they serve the four forward hops and the -x hop), and per backward hop the one link
+// per site of the neighbour row, an N_c x N_c block of its four.  LL 1 (FP64): one direction at a time, the own links as
+// well; a 72-byte block per 288-byte site, the own links are then 128-byte lines touched four times far apart, which costs
+// FP32 2 to 3 % (100.6 against 98.0 us at 16^3 x 32, N_c = 3, N_v = 12, bound by the fabric, since a row leaves L2 between
+// its seven uses), while FP64, at two wavefronts per SIMD, does not hide the larger first load (216.5 against 224.1 us; N_c = 2
+// at 32 x 12 x 12 x 16 83.5 against 96.6).  LL 0: every thread loads its own link one direction ahead.
+// CLOV 2: the site's clover record is staged as well (contiguous, 16 bytes a lane) instead of being read by every
+// right-hand side's thread (with the links 1.70 against 1.63 ms for BF16 vectors at 32^3 x 64, which the vector
+// instructions bound: 1.46 ms with the BF16 stores converted in hardware).  CLOV 1: every thread reads the record; CLOV 0:
+// no clover field.  launch_rows chooses.
 
 // Entries of a neighbour row's links (one direction) that a thread moves: N_c^2 over the threads of a site, at most
 // three of them where N_v is only known at run time.
@@ -236,7 +239,7 @@ struct RowLinks {
     static constexpr int PER = NVC > 0 ? (NC * NC + NVC / RB - 1) / (NVC / RB) : 3;
 };
 
-template <int NC, int RB, bool DAG, class P, int NVC, bool LL, int CLOV>
+template <int NC, int RB, bool DAG, class P, int NVC, int LL, int CLOV>
 __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* __restrict__ U,
                                                           const typename P::S* __restrict__ in,
                                                           typename P::S* __restrict__ out, typename P::R diag,
@@ -299,7 +302,7 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
     u32x4* const lown_u = rtile + rt.S * SU;
     const uint32_t own_units = nlink * 4u * static_cast<uint32_t>(sizeof(G)) / 16u;
     const G* lown = reinterpret_cast<const G*>(lown_u);
-    u32x4* const lwin_u = lown_u + (LL ? own_units : 0u);
+    u32x4* const lwin_u = lown_u + (LL == 2 ? own_units : 0u);
     G* const lwin = reinterpret_cast<G*>(lwin_u);
     u32x4* const lclov_u = lwin_u + (LL ? (nlink * static_cast<uint32_t>(sizeof(G)) + 15u) / 16u : 0u);
     auto stage = [&](u32x4* dst, const u32x4* from, uint32_t n) __attribute__((always_inline)) {
@@ -344,8 +347,10 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
     const int xm = x == 0 ? g.nx - 1 : x - 1;
     cx<R> lxp[NC][NC], lxm[NC][NC], lnext[NC][NC];
     fetch(rowsite);
-    if constexpr (LL) {
+    if constexpr (LL == 2) {
         stage(lown_u, reinterpret_cast<const u32x4*>(U + rowsite * 4 * L), own_units);
+    } else if constexpr (LL == 1) {
+        lfetch(rowsite, 0);
     } else {
         load_link<NC, false, P>(lxp, U + (site * 4 + 0) * L);
         load_link<NC, true, P>(lxm, U + ((rowsite + xm) * 4 + 0) * L);
@@ -355,8 +360,10 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
         stage(lclov_u, reinterpret_cast<const u32x4*>(clov) + rowsite * CU, static_cast<uint32_t>(rt.S) * CU);
     }
     stash();
+    if constexpr (LL == 1) lstash();
     __syncthreads();
     fetch(row_neighbour_start(pos, 0, g));
+    if constexpr (LL == 1) lfetch(rowsite, 1);
     auto mass_term = [&]() __attribute__((always_inline)) {
         const S* mine = at(j);
 #pragma unroll
@@ -373,9 +380,12 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
     // taken into registers
     if constexpr (CLOV)
         if (active) mass_term();
-    if constexpr (LL) {
+    if constexpr (LL == 2) {
         load_link<NC, false, P>(lxp, lown + x * 4 * L);
         load_link<NC, true, P>(lxm, lown + xm * 4 * L);
+    } else if constexpr (LL == 1) {
+        load_link<NC, false, P>(lxp, lwin + x * L);
+        load_link<NC, true, P>(lxm, lwin + xm * L);
     } else {
         load_link<NC, false, P>(lnext, U + (site * 4 + 1) * L);
     }
@@ -391,7 +401,7 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
         constexpr bool BACK = decltype(back_c)::value;
         constexpr int DIR = 2 * (MU - 1) + (BACK ? 1 : 0);
         cx<R> lcur[NC][NC];
-        if constexpr (!LL) {
+        if constexpr (LL == 0) {
 #pragma unroll
             for (int a = 0; a < NC; ++a)
 #pragma unroll
@@ -399,22 +409,26 @@ __global__ __launch_bounds__(512) void wilson_rows_kernel(const typename P::G* _
         }
         __syncthreads();
         stash();
-        if constexpr (LL && BACK) lstash();
+        if constexpr (LL == 1 || (LL == 2 && BACK)) lstash();
         __syncthreads();
         if constexpr (DIR < 5) {
             constexpr int ND = DIR + 1;
             constexpr int NMU = ND / 2 + 1;
             const int64_t nrow = row_neighbour_start(pos, ND, g);
             fetch(nrow);
-            if constexpr (LL) {
-                if constexpr (ND % 2 == 1) lfetch(nrow, NMU);
+            if constexpr (LL != 0) {
+                if constexpr (ND % 2 == 1)
+                    lfetch(nrow, NMU);
+                else if constexpr (LL == 1)
+                    lfetch(rowsite, NMU);
             } else if constexpr (ND % 2 == 0) {
                 load_link<NC, false, P>(lnext, U + (site * 4 + NMU) * L);
             } else {
                 load_link<NC, true, P>(lnext, U + ((nrow + x) * 4 + NMU) * L);
             }
         }
-        if constexpr (LL) load_link<NC, BACK, P>(lcur, BACK ? lwin + x * L : lown + (x * 4 + MU) * L);
+        if constexpr (LL != 0)
+            load_link<NC, BACK, P>(lcur, BACK || LL == 1 ? lwin + x * L : lown + (x * 4 + MU) * L);
         if (active) {
             const bool wrap = MU == 3 && g.apbc && ct == (BACK ? 0 : g.nt - 1);  // fermion sign
             hop_with<NC, RB, MU, (BACK ? -SF : SF), P, NVC>(acc, lcur, at(j), nv,
@@ -484,19 +498,38 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     if (!row_order(4, a.g, rt)) return false;
     const int block = (rt.threads + 63) / 64 * 64;
     size_t lds = row_tile_lds(rt.S, units, pad);
-    // the links (and the clover field) staged in LDS after the row tile, where a thread moves at most LPER entries of a
-    // neighbour row's links and the device has the room (beyond the row tile's own cap)
-    const size_t nlink = static_cast<size_t>(rt.S) * NC * NC * sizeof(typename P::G);
-    const size_t lds_cl = static_cast<size_t>(rt.S) * clover_reals<NC>() * sizeof(typename P::R);
-    const bool stage_cl = a.clover && reinterpret_cast<uintptr_t>(a.clover) % 16 == 0 && lds + lds_cl <= max_lds_per_block();
-    if (stage_cl) lds += lds_cl;
-    const size_t lds_ll = lds + 4 * nlink + (nlink + 15) / 16 * 16;
-    // FP64 takes it at N_v = 12 only: with N_v known at run time the entries in flight spill (24^3 x 48, N_v = 4: 0.69
-    // against 0.55 ms with a link per thread)
+    // What is staged in LDS after the row tile, with N_c^2 links of a site moved by its threads, at most LPER each, and up to
+    // all of the LDS, beyond the row tile's own cap (one work-group per CU instead of two costs nothing: FP32, N_v = 24 at
+    // 32 x 16^3 274 against 284 us).
+    // FP32, BF16: the links from 8 right-hand sides on, or where links and vectors leave the 256 MB of the Infinity Cache;
+    // below that a thread moves two or three entries and waits for them (BF16, N_v = 4: 31.7 against 28.4 us at 32 x 16^3,
+    // but 215 against 250 at 32^4).  With them the clover records from 10 on, when they are read by that many threads
+    // (FP32 at 16^3 x 32: N_v = 4 55.2 against 48.6 us, 10 97.5 and 98.4, 24 253 and 353); without the links they cost
+    // (BF16, N_v = 12: 137 against 108).
+    // FP64: the links at N_v = 12 (with N_v known at run time the entries in flight spill: N_v = 4 at 24^3 x 48 0.69 against
+    // 0.55 ms), the clover records from 5 right-hand sides on where as many work-groups still share a CU (N_v = 8 at
+    // 16^3 x 32 200 against 218 us, N_v = 4 at 64 x 8 x 16^2 135 against 122).
     constexpr bool kFP64 = sizeof(typename P::R) == 8;
-    const bool ll = NC * NC <= RowLinks<NC, RB, 0>::PER * nrg && lds_ll <= max_lds_per_block() &&
-                    (!kFP64 || (a.nv == 12 && RB == 1));
-    if (ll) lds = lds_ll;
+    const size_t room = max_lds_per_block();
+    const size_t nlink = static_cast<size_t>(rt.S) * NC * NC * sizeof(typename P::G);
+    const size_t lds_ll = (kFP64 ? 0 : 4 * nlink) + (nlink + 15) / 16 * 16;
+    const size_t lds_cl = static_cast<size_t>(rt.S) * clover_reals<NC>() * sizeof(typename P::R);
+    const double data = static_cast<double>(a.g.vol) * (4.0 * NC * NC * sizeof(typename P::G) + 2.0 * block_bytes);
+    const bool ll = NC > 1 && NC * NC <= RowLinks<NC, RB, 0>::PER * nrg && lds + lds_ll <= room &&
+                    (kFP64 ? a.nv == 12 && RB == 1 : a.nv >= (a.clover ? 10 : 8) || data > 256e6);
+    if (ll) lds += lds_ll;
+    bool stage_cl = a.clover && reinterpret_cast<uintptr_t>(a.clover) % 16 == 0 && lds + lds_cl <= room;
+    if constexpr (kFP64) {
+        constexpr size_t kPerSimd = NC == 1 ? (RB == 1 ? 6 : 4) : (NC == 2 && RB == 1 ? 3 : 2);  // wavefronts, by registers
+        const size_t by_registers = std::max<size_t>(1, 4 * kPerSimd / (block / 64));
+        stage_cl = stage_cl && a.nv >= 5 &&
+                   std::min(room / (lds + lds_cl), by_registers) >= std::min(room / lds, by_registers);
+        // N_c = 4 spills 456 registers with the record read by every thread: 159 us at 128 x 8^3, N_v = 2, direct 67
+        if (NC == 4 && a.clover && !stage_cl) return false;
+    } else {
+        stage_cl = stage_cl && ll && a.nv >= 10;
+    }
+    if (stage_cl) lds += lds_cl;
     const dim3 grid(static_cast<unsigned>(grid_blocks_x8(rt.ntiles, 1)));
     using R = typename P::R;
     const R diag = static_cast<R>(4.0 + a.mass);
@@ -514,38 +547,35 @@ bool launch_rows(const StencilArgs& a, hipStream_t st) {
     };
     // the clover term is a separate instantiation: its registers would otherwise lower the occupancy
     // of the plain kernel
-    auto pick = [&](auto clov_c) {
-        constexpr int CL = decltype(clov_c)::value;
-        if (ll) {
-            if constexpr (RB == 1) {
-                if (a.nv == 12) {  // the RHS stride as a compile-time constant
-                    if (a.dagger)
-                        go(wilson_rows_kernel<NC, RB, true, P, 12, true, CL>);
-                    else
-                        go(wilson_rows_kernel<NC, RB, false, P, 12, true, CL>);
-                    return;
-                }
-            }
-            if constexpr (!kFP64) {
-                if (a.dagger)
-                    go(wilson_rows_kernel<NC, RB, true, P, 0, true, CL>);
-                else
-                    go(wilson_rows_kernel<NC, RB, false, P, 0, true, CL>);
+    auto pick = [&](auto clov_c, auto links_c) {
+        constexpr int CL = decltype(clov_c)::value, LL = decltype(links_c)::value;
+        auto with = [&](auto nvc) {
+            constexpr int NVC = decltype(nvc)::value;
+            if (a.dagger)
+                go(wilson_rows_kernel<NC, RB, true, P, NVC, LL, CL>);
+            else
+                go(wilson_rows_kernel<NC, RB, false, P, NVC, LL, CL>);
+        };
+        if constexpr (RB == 1 && LL != 0) {
+            if (a.nv == 12) {  // the RHS stride as a compile-time constant
+                with(std::integral_constant<int, 12>{});
                 return;
             }
         }
-        // runtime RHS stride, links loaded by every thread
-        if (a.dagger)
-            go(wilson_rows_kernel<NC, RB, true, P, 0, false, CL>);
-        else
-            go(wilson_rows_kernel<NC, RB, false, P, 0, false, CL>);
+        if constexpr (!kFP64 || LL == 0) with(std::integral_constant<int, 0>{});
     };
+    const std::integral_constant<int, 0> none;
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    const std::integral_constant<int, kFP64 ? 1 : 2> links;
     if (!clov)
-        pick(std::integral_constant<int, 0>{});
+        ll ? pick(none, links) : pick(none, none);
     else if (!stage_cl)
-        pick(std::integral_constant<int, 1>{});
-    else
-        pick(std::integral_constant<int, 2>{});
+        ll ? pick(one, links) : pick(one, none);
+    else if (ll)
+        pick(two, links);
+    else if constexpr (kFP64)
+        pick(two, none);
     return ok;
 }
 

@@ -101,6 +101,23 @@ def test_clover_apply_small(case, op, prec, variant):
         dirac.set_launch_shape(op, prec, 0, 0)
 
 
+# (dims, nc, nv): what the Wilson row kernel stages beside the row: nothing, the links, links and clover records, with one
+# and with two right-hand sides per thread, and more than 64 KiB of LDS (n_x >= 24)
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("dims,nc,nv", [((16, 2, 2, 2), 3, 4), ((12, 2, 3, 2), 3, 8), ((16, 2, 2, 3), 3, 12),
+                                        ((11, 3, 2, 2), 2, 13), ((24, 2, 2, 2), 3, 24), ((32, 2, 2, 2), 3, 12),
+                                        ((24, 2, 2, 2), 3, 20), ((8, 2, 3, 2), 4, 12), ((16, 2, 2, 2), 1, 12)])
+def test_wilson_clover_staging(dims, nc, nv, prec):
+    rng = np.random.default_rng(340 + nv)
+    Ud, Uo = _links(si.gauge_field(rng, dims, nc, "haar"), prec)
+    ud, u_in = _vec(si.wilson_vector(rng, dims, nc, nv), prec)
+    C = dirac.clover_field(Ud, 1.0)
+    cu = clover_apply(field_strength(Uo), u_in, 1.0)
+    for dagger in (False, True):
+        v = _host((dirac.apply_dagger if dagger else dirac.apply)("wilson", Ud, ud, 0.08, clover=C), prec)
+        parity(v, DIRAC[("wilson", dagger)](Uo, u_in, 0.08, True) + cu, TOL[prec], (dims, nc, nv, prec, dagger))
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
 @pytest.mark.parametrize("dims,nc,nv", [((16, 2, 2, 3), 3, 12), ((12, 2, 3, 2), 3, 8), ((16, 3, 2, 2), 2, 4),
                                         ((64, 2, 2, 2), 4, 1)])
