@@ -20,7 +20,7 @@ namespace dirac {
 namespace {
 
 // Lanes of a gradient kernel: a site has one lane per spin component that the kernel keeps apart (Wilson: two half
-// spinor rows, Brillouin: four spins, staggered: none) and RL right-hand sides r = lane, lane + RL, ...  A vector is
+// spinor rows, Brillouin: four spins, staggered: none, but directions) and RL right-hand sides r = lane, lane + RL, ...  A vector is
 // [site][colour][spin][rhs], so the lanes of a site read one contiguous run, whole lines for N_v = 4, and a line is
 // not asked for again once it has left the cache.  RL is 4 (more would leave lanes idle for a few right-hand sides),
 // less for fewer than 3 right-hand sides.  The lanes' sums are added inside a row of 16 lanes by DPP moves and lane k
@@ -275,18 +275,26 @@ __global__ __launch_bounds__(kForceThreads) void wilson_force_kernel(const doubl
     wilson_force_mu<NC, RL, 3>(psi, chi, gout, coeff, g, nv, f, c, own);
 }
 
+// A lane takes one or two of a site's four directions, and a site has 4 / DIRS RL lanes.  All four in one lane are too long a
+// chain of loads: at 24^4 with N_c = 3 126 us for N_v = 1, 168 for 3, 510 for 12; with one each 79, 125 and 296.  Two where 16
+// lanes per site do not read whole lines (24^4, N_v = 8: N_c = 1 41 against 47 us, N_c = 4 309 and 314; 16^3 x 32 88 and 112).
+template <int NC, int RL>
+constexpr int kStaggeredDirs = RL < 4 || NC == 3 ? 1 : 2;
 template <int NC, int RL>
 __global__ __launch_bounds__(kForceThreads) void staggered_force_kernel(const double2* __restrict__ psi,
                                                                         const double2* __restrict__ chi,
                                                                         double2* __restrict__ gout, double coeff,
                                                                         Geom g, int nv, SiteOrder order, int64_t first) {
+    constexpr int DIRS = kStaggeredDirs<NC, RL>, LANES = 4 / DIRS * RL;  // lanes of a site: direction, right-hand side
     const int64_t block = first + logical_block();
-    if (block * (kForceThreads / RL) >= g.vol) return;
-    const ForceLane f = force_lane<RL>(block, order, g);
+    if (block * (kForceThreads / LANES) >= g.vol) return;
+    ForceLane f = force_lane<LANES>(block, order, g);
+    const int mu0 = f.lane / RL * DIRS;
+    f.lane %= RL;
     const Coord c = site_coord(f.site, g);
     const int64_t vs = static_cast<int64_t>(NC) * nv;
 #pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {
+    for (int mu = mu0; mu < mu0 + DIRS; ++mu) {
         bool wraps;
         const int64_t fwd = f.site + step_forward(c, mu, g, wraps);
         GradOut<NC, RL> out;
@@ -351,8 +359,8 @@ __global__ __launch_bounds__(256) void project_kernel(const double2* __restrict_
 template <int NC, int RL>
 void launch_force_rl(dirac_op op, int nv, const Geom& g, const void* psi, const void* chi, void* gout, double coeff,
                      hipStream_t st) {
-    const int sites = kForceThreads / (RL * (op == DIRAC_BRILLOUIN ? 4 : (op == DIRAC_WILSON ? 2 : 1)));  // per block
-    const int64_t tiles = (g.vol + sites - 1) / sites;
+    const int lanes = RL * (op == DIRAC_BRILLOUIN ? 4 : (op == DIRAC_WILSON ? 2 : 4 / kStaggeredDirs<NC, RL>));  // of a site
+    const int64_t tiles = (g.vol + kForceThreads / lanes - 1) / (kForceThreads / lanes);
     const int64_t blocks = op == DIRAC_BRILLOUIN ? tiles * (40 / kForceDirs) : tiles;
     auto p = static_cast<const double2*>(psi);
     auto c = static_cast<const double2*>(chi);
@@ -374,7 +382,8 @@ void launch_force_rl(dirac_op op, int nv, const Geom& g, const void* psi, const 
 template <int NC>
 int launch_force_nc(dirac_op op, int nv, const Geom& g, const void* psi, const void* chi, void* gout, double coeff,
                     hipStream_t st) {
-    switch (force_lanes(nv)) {
+    // N_c = 1, staggered: a vector is a run of N_v elements, and one lane loads it whole (24^4, N_v = 2: 16 against 25 us)
+    switch (NC == 1 && op == DIRAC_STAGGERED && nv <= 3 ? 1 : force_lanes(nv)) {
         case 1: launch_force_rl<NC, 1>(op, nv, g, psi, chi, gout, coeff, st); break;
         case 2: launch_force_rl<NC, 2>(op, nv, g, psi, chi, gout, coeff, st); break;
         default: launch_force_rl<NC, 4>(op, nv, g, psi, chi, gout, coeff, st); break;
