@@ -135,11 +135,12 @@ __device__ __forceinline__ Mat<NC> field_from(const Mat<NC>& q) {
 
 // Bound by the latency of its chains of links and products, at two wavefronts per SIMD at 16^3 x 32 (a thread per plane
 // was no faster).  Each XCD takes a contiguous range of sites, whose neighbours its L2 then holds: 103 us against 112
-// (FP32, N_c = 3).
+// (FP32, N_c = 3).  Not for N_c = 4, whose spilled registers fill the L2 (24^4: 762 us, 732 in the hardware's order; FP64 1023,
+// 958).
 template <int NC, typename GI, typename CO>
 __global__ __launch_bounds__(128) void clover_field_kernel(const GI* __restrict__ U, CO* __restrict__ out, double csw,
                                                            Geom g) {
-    const int64_t site = logical_block() * blockDim.x + threadIdx.x;
+    const int64_t site = (NC == 4 ? static_cast<int64_t>(blockIdx.x) : logical_block()) * blockDim.x + threadIdx.x;
     if (site >= g.vol) return;
     const Coord co = site_coord(site, g);
     const int n[4] = {co.x, co.y, co.z, co.t};
