@@ -283,6 +283,112 @@ __global__ __launch_bounds__(kStoutLinks * NC) void stout_kernel(const double2* 
     if (l.active) put_row<NC>(V + (l.site * 4 + l.mu) * L, l.i, mul(E, whole<NC>(up)));
 }
 
+// The same with one thread per link, which holds whole matrices: the threads of a link otherwise read every right factor
+// N_c times.  Faster where the links fill the chip (N_c = 4: 24^4 891 against 1200 us, 8^3 x 16 34 and 34, 4^4 29 against 21;
+// N_c = 3: 16^3 x 8 46 against 55, 24^4 418 and 419, 4^4 14 against 11) and for N_c = 1 (18 against 21 us at 16^3 x 32), not
+// for N_c = 2 (24^4 167 against 142).
+template <int NC>
+constexpr int64_t kStoutLinkSites = NC == 1 ? 0 : (NC == 2 ? INT64_MAX : 8192);  // from this volume on
+template <int N>
+__device__ __forceinline__ CM<N> mul(const CM<N>& a, const CM<N>& b) {
+    CM<N> r;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            cx<double> s{0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < N; ++k) cfma(s, a.e[i][k], b.e[k][j]);
+            r.e[i][j] = s;
+        }
+    return r;
+}
+template <int N>
+__device__ __forceinline__ CM<N> adjoint(const CM<N>& a) {
+    CM<N> r;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) r.e[i][j] = cconj(a.e[j][i]);
+    return r;
+}
+template <int N>
+__device__ __forceinline__ void add_to(CM<N>& a, const CM<N>& b) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) a.e[i][j] = cadd(a.e[i][j], b.e[i][j]);
+}
+template <int N>
+__device__ __forceinline__ CM<N> scaled(const CM<N>& a, double s) {
+    CM<N> r;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) r.e[i][j] = cscale(s, a.e[i][j]);
+    return r;
+}
+
+template <int NC>
+__global__ __launch_bounds__(128) void stout_link_kernel(const double2* __restrict__ U, double2* __restrict__ V,
+                                                         double rho, Geom g, int64_t first) {
+    constexpr int L = NC * NC;
+    const int64_t link = (first + logical_block()) * blockDim.x + threadIdx.x;
+    if (link >= 4 * g.vol) return;
+    const int64_t site = link >> 2;
+    const int mu = static_cast<int>(link & 3);
+    const Coord c = site_coord(site, g);
+    CM<NC> x;  // the staples, then Omega, then i Q
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) x.e[i][j] = {0.0, 0.0};
+    const int64_t n_mu = shifted(c, mu, 1, g);
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        const int nu = k + (k >= mu);
+        const int64_t n_nu = shifted(c, nu, 1, g), m_nu = shifted(c, nu, -1, g), m_nu_p_mu = shifted2(c, nu, -1, mu, 1, g);
+        add_to(x, mul(mul(whole<NC>(U + (site * 4 + nu) * L), whole<NC>(U + (n_nu * 4 + mu) * L)),
+                      adjoint(whole<NC>(U + (n_mu * 4 + nu) * L))));
+        add_to(x, mul(mul(adjoint(whole<NC>(U + (m_nu * 4 + nu) * L)), whole<NC>(U + (m_nu * 4 + mu) * L)),
+                      whole<NC>(U + (m_nu_p_mu * 4 + nu) * L)));
+    }
+    const CM<NC> u = whole<NC>(U + link * L);
+    x = mul(scaled(x, rho), adjoint(u));
+    double tr = 0.0;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) tr += x.e[i][i].im;
+    const CM<NC> d = adjoint(x);
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            x.e[i][j] = cscale(0.5, csub(x.e[i][j], d.e[i][j]));
+            if (i == j) x.e[i][j].im -= tr / NC;
+        }
+    int s = 0;  // the series and squarings of exp_rows
+    for (double nrm = norm1(x); nrm > 0.25 && s < 40; nrm *= 0.5) ++s;
+    x = scaled(x, ldexp(1.0, -s));
+    CM<NC> T, E;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) T.e[i][j] = E.e[i][j] = {i == j ? 1.0 : 0.0, 0.0};
+#pragma unroll 1
+    for (int k = 1; k <= kExpTerms; ++k) {
+        T = scaled(mul(T, x), 1.0 / k);
+        add_to(E, T);
+    }
+#pragma unroll 1
+    for (int q = 0; q < s; ++q) E = mul(E, E);
+    const CM<NC> v = mul(E, u);
+    double2* o = V + link * L;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) o[i * NC + j] = make_double2(v.e[i][j].re, v.e[i][j].im);
+}
+
 // gU += the gradient with respect to U of L(U'(U)) given gV = dL/dU' (one stout step).  A link passes the gradient of
 // its staple products, G_P, on to the 18 links of its staples.  With a workspace (SCATTER false) the link's own part
 // and G_P are stored there, two link fields, and stout_gather_kernel collects the 18 parts of every link; without,
@@ -658,6 +764,12 @@ int launch_nc(int which, const Geom& g, const void* a, const void* b, void* out,
     };
     const int64_t groups = (4 * g.vol + kStoutLinks - 1) / kStoutLinks;
     if (which == 0) {
+        if constexpr (kStoutLinkSites<NC> != INT64_MAX) {
+            if (g.vol >= kStoutLinkSites<NC>) {
+                slices((4 * g.vol + 127) / 128, 128, stout_link_kernel<NC>, A, O, rho);
+                return DIRAC_OK;
+            }
+        }
         slices(groups, kStoutLinks * NC, stout_kernel<NC>, A, O, rho);
     } else if (which == 1) {
         auto w = static_cast<double2*>(ws);

@@ -87,6 +87,25 @@ def test_stout_step_ragged_groups(nc, dims, rho):
     assert np.max(np.abs(host(out) - base - gU)) < 1e-13 * max(1.0, np.max(np.abs(gU)))
 
 
+@pytest.mark.parametrize("nc", [1, 3, 4])
+@pytest.mark.parametrize("rho", [0.12, 2.5])
+def test_stout_step_thread_per_link(nc, rho):
+    """A volume (8208 sites, the last work-group partly empty) whose links have one thread each."""
+    rng = np.random.default_rng(690 + nc)
+    U = si.gauge_field(rng, (8, 9, 6, 19), nc, "haar")
+    assert np.max(np.abs(host(dirac.stout_step(to_dev(U), rho)) - stout_step(U, rho))) < (1e-13 if rho < 1 else 1e-11)
+
+
+@pytest.mark.parametrize("nc,dims", [(2, (3, 3, 3, 5)), (3, (5, 3, 3, 3)), (4, (2, 3, 2, 3))])
+def test_stout_backward_with_workspace_repeats_bit_for_bit(nc, dims):
+    """With a workspace the gradient is gathered in a fixed order: into zeros, the same bits every time."""
+    rng = np.random.default_rng(695 + nc)
+    U, R = to_dev(si.gauge_field(rng, dims, nc, "haar")), to_dev(_cg(rng, dims[::-1] + (4, nc, nc)))
+    first = dirac.stout_backward(U, R, 0.12)
+    for _ in range(3):
+        assert torch.equal(first, dirac.stout_backward(U, R, 0.12))
+
+
 @pytest.mark.parametrize("nc", [2, 3])
 def test_links_backward_against_differences(nc):
     dims = (2, 2, 4, 4)
