@@ -120,7 +120,8 @@ int dirac_apply_normal(dirac_op op, dirac_prec prec, const void* gauge, const vo
  *   overlap U.  Errors: EINVAL, EUNSUPPORTED (nc), EHIP.
  * dirac_apply_clover / dirac_apply_clover_dagger: v = (D + C) u and v = (D + C)^dagger u = D^dagger u + C u
  *   (C is hermitian) for op DIRAC_WILSON or DIRAC_BRILLOUIN (Eqs. def_wils, def_bril with c_SW > 0);
- *   otherwise as dirac_apply.  clover comes from dirac_clover_field in the precision of `prec`.
+ *   otherwise as dirac_apply.  clover comes from dirac_clover_field in the precision of `prec`.  It need
+ *   not be 16-byte aligned, but only an aligned one is staged through LDS (Wilson).
  */
 size_t dirac_clover_field_bytes(dirac_prec prec, int nc, const dirac_dims* dims);
 int dirac_clover_field(dirac_prec prec, const void* U, double csw, void* clover, int nc, const dirac_dims* dims,
@@ -287,8 +288,8 @@ int bicgstab_solve(dirac_op op, dirac_prec outer, dirac_prec inner, const void* 
  * Brillouin Laplacian 1; used whenever it divides the columns; the Wilson Laplacian sees 4 Nv columns);
  * variant = 0 automatic, 1 direct global loads (one thread per site and rb columns), 4 row tiles
  * (a work-group stages one x-row of the lattice and its neighbour rows in LDS with contiguous loads,
- * the next row in flight while the current one is consumed; Wilson with Nv = 12 and staggered in
- * FP32/BF16 also stage each direction's links in LDS; the Brillouin kernels walk the 27 neighbouring
+ * the next row in flight while the current one is consumed; Wilson and, in FP32/BF16, staggered also
+ * stage links in LDS where that is faster; the Brillouin kernels walk the 27 neighbouring
  * x-rows with a window of three links per site).  Row tiles fall back to direct loads for shapes they
  * cannot take.  Results agree to rounding whatever the shape.  Process-wide, not thread-safe. */
 int dirac_set_launch_shape(dirac_op op, dirac_prec prec, int rb, int variant);

@@ -8,8 +8,9 @@
 // dL = Re Tr(G^+ dM).  For a product the gradient of a factor is (left part)^+ G (right part)^+; for
 // E = exp(X) it is L(X^+, G_E), the Frechet derivative of exp at X^+ in the direction G_E (the adjoint
 // of L(X, .) for this inner product), read off the upper right block of exp([[X^+, G_E], [0, X^+]]).
-// All arithmetic FP64 (complex128 links and gradients).  The stout gradients are accumulated with atomic adds,
-// so the order of the additions (and the last bits of the result) can differ from run to run.
+// All arithmetic FP64 (complex128 links and gradients).  With a workspace the stout gradients are gathered in a fixed
+// order (the same bits from run to run); without one they are accumulated with atomic adds, whose order and so the
+// last bits of the result can differ.
 #include <type_traits>
 
 #include "common.h"
@@ -25,7 +26,8 @@ struct CM {
     cx<double> e[N][N];
 };
 
-// The kernels of a smearing step give a link N_c threads: thread i owns row i of every matrix, so that a product
+// The row kernels of a smearing step (the backward passes, and the forward pass where stout_link_kernel does not take
+// it) give a link N_c threads: thread i owns row i of every matrix, so that a product
 // row x matrix needs no exchange and only the right factor is held whole.  Rows meet in LDS where a whole matrix or
 // an adjoint's row is needed.  A work-group takes kStoutLinks links; each XCD takes a contiguous range of them, whose
 // neighbours its L2 then holds (a gather 38 against 39.7 us, a step's first kernel 26.1 against 27.0, at 8^3 x 16).

@@ -37,9 +37,10 @@ import re
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 COPY_BYTES = 512 * 2 ** 20
 SOURCES = {
-    "wilson": "paper_2112_14640_amd/csrc/wilson_kernels.h",
-    "staggered": "paper_2112_14640_amd/csrc/staggered.hip",
-    "brillouin": "paper_2112_14640_amd/csrc/brillouin_kernels.h",
+    "wilson": ["paper_2112_14640_amd/csrc/wilson_kernels.h"],
+    "staggered": ["paper_2112_14640_amd/csrc/staggered.hip"],
+    "brillouin": ["paper_2112_14640_amd/csrc/brillouin_kernels.h", "paper_2112_14640_amd/csrc/brillouin_plan.h"],
+    "links": ["paper_2112_14640_amd/csrc/links.hip"],
 }
 COMMON = ["paper_2112_14640_amd/csrc/common.h", "paper_2112_14640_amd/csrc/tile.h",
           "paper_2112_14640_amd/csrc/kernels.h", "paper_2112_14640_amd/csrc/api.hip"]
@@ -146,7 +147,7 @@ def main():
         fb = fetch[key] * 1024 * f_scale
         wb = write[key] * 1024 * w_scale
         alg = algorithmic_bytes(op)
-        srcs = [SOURCES["brillouin" if op == "links" else op]] + COMMON
+        srcs = SOURCES[op] + COMMON
         table[f"{key}_fp32_16x32_nv12" if op != "links" else "links_fp32_16x32"] = {
             "bytes_per_launch": int(round(fb + wb)), "fetch_bytes": int(round(fb)), "write_bytes": int(round(wb)),
             "algorithmic_bytes": alg, "sources": srcs, "source_hash": source_hash(srcs)}
